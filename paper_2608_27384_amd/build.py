@@ -15,7 +15,7 @@ CSRC = os.path.join(HERE, "csrc")
 ROOT = os.path.dirname(HERE)
 OUT = os.path.join(HERE, "libflashvla.so")
 BUILD_DIR = os.path.join(ROOT, "_build")
-SOURCES = ["fv_runtime.hip", "fv_gemm.hip", "fv_attn.hip", "fv_misc.hip"]
+SOURCES = ["fv_runtime.hip", "fv_gemm.hip", "fv_attn.hip", "fv_few.hip", "fv_misc.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [

@@ -911,6 +911,208 @@ __global__ __launch_bounds__(64 * NWV) void attn16d_kernel(AttnArgs a) {
   pre.retire();
 }
 
+// Few-row passes: a workgroup takes 16 query rows of one (stream, kv head)
+// and one key split; its four waves take key tiles of their own (wave w the
+// tiles w, w + 4, .. of the split), read K and V^T straight from memory as
+// MFMA fragments (no operand is shared, so LDS would only add a pass) and
+// merge their sums in LDS once.  Small row tiles because the few rows must
+// spread over the chip: a CU takes in 20-30 bytes of K/V a clock, so 25
+// workgroups with all keys each took 33 us at 50 rows and 866 keys.  The
+// next tile's K is requested when this tile's scores are formed and its V^T
+// after the product.  Rows, masks and the fixed-reference softmax are those
+// of attn16d_kernel; a wave sees few tiles, so it rescales in the loop when
+// a row passes the headroom.
+constexpr int kFewAttnWaves = 4;
+template <int DH> constexpr int few_attn_lds() {
+  return kFewAttnWaves * 16 * (DH + 4) * 4;
+}
+template <typename T, int DH>
+__global__ __launch_bounds__(64 * kFewAttnWaves) void attn_few_kernel(AttnArgs a) {
+  constexpr int NW = kFewAttnWaves;
+  constexpr bool kBF16 = sizeof(T) == 2;
+  constexpr int E = 16 / (int)sizeof(T);   // elements per 16-byte piece
+  constexpr int KT = 4 * E;                // keys per tile
+  constexpr int NH = kBF16 ? 2 : 1;        // 16-key halves of a tile
+  constexpr int NKS = DH / KT, NDT = DH / 16;
+  constexpr int NP = 4 * NH;               // probabilities per lane and tile
+  constexpr int LDO = DH + 4;
+  extern __shared__ __attribute__((aligned(16))) float few_so[];  // [NW][16][LDO]
+  __shared__ float sml[NW][16][2];
+
+  const int G = a.n_q_heads / a.n_kv_heads;
+  const int rows_bg = a.tokens * G;
+  const int tile0 = blockIdx.x * 16;
+  const int b = blockIdx.y / a.n_kv_heads, g = blockIdx.y - b * a.n_kv_heads;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int P = a.len[b];
+  const int C = a.chunk_len;
+  const int l16 = lane & 15, lg = lane >> 4;
+  const int K = a.tokens / C;
+  const int first = K - a.n_valid[b];
+  const int rqc = min(tile0 + l16, rows_bg - 1);
+  const int tok = rqc / G;
+  const int head = g * G + (rqc - tok * G);
+  int klo, khi;  // this row's visible buffer keys [klo, khi); prefix keys [0, P)
+  visible_chunks(tok / C, K, first, a.mask_mode, klo, khi);
+  klo = buffer_row0(P) + C * klo;
+  khi = buffer_row0(P) + C * khi;
+  const int rlast = min(tile0 + 15, rows_bg - 1);
+  const KeyTiles kts = key_tiles(P, C, K, first, a.mask_mode, tile0 / G, rlast / G, KT);
+  const int split = blockIdx.z;
+  const int kt_begin = (split * kts.n) / a.n_split + wave, kt_end = ((split + 1) * kts.n) / a.n_split;
+
+  const T* kbase = reinterpret_cast<const T*>(a.karena) +
+                   ((size_t)b * a.n_kv_heads + g) * (size_t)a.S * DH;
+  const T* vbase = reinterpret_cast<const T*>(a.vtarena) +
+                   ((size_t)b * a.n_kv_heads + g) * (size_t)DH * a.S;
+  const float sl2 = 1.4426950408889634f / sqrtf((float)DH);
+  // score operand row i of half h is key 8 (i / 4) + 4 h + i % 4 (bf16) or i,
+  // so a lane's NP scores are keys NP lg .. in order
+  const int krow = kBF16 ? 8 * (l16 >> 2) + (l16 & 3) : l16;
+  const T* kp = kbase + (size_t)krow * DH + E * lg;
+  const T* vp = vbase + (size_t)l16 * a.S + E * lg;
+
+  u32x4 kf[NKS][NH], vf[NDT], qf[NKS];
+  auto load_k = [&](int vt) __attribute__((always_inline)) {
+    const T* p = kp + (size_t)kts.tile(vt) * KT * DH;
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks)
+#pragma unroll
+      for (int h = 0; h < NH; ++h)
+        kf[ks][h] = *reinterpret_cast<const u32x4*>(p + 4 * h * DH + KT * ks);
+  };
+  auto load_v = [&](int vt) __attribute__((always_inline)) {
+    const T* p = vp + kts.tile(vt) * KT;
+#pragma unroll
+    for (int dt = 0; dt < NDT; ++dt)
+      vf[dt] = *reinterpret_cast<const u32x4*>(p + (size_t)16 * dt * a.S);
+  };
+  {
+    const T* qrow = reinterpret_cast<const T*>(a.q) +
+                    ((size_t)(b * a.tokens + tok) * a.n_q_heads + head) * DH + E * lg;
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks) qf[ks] = *reinterpret_cast<const u32x4*>(qrow + KT * ks);
+  }
+  f32x4 acc[NDT];
+#pragma unroll
+  for (int dt = 0; dt < NDT; ++dt) acc[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float m_run = -INFINITY, l_run = 0.f;  // l_run: this lane's share of the row sum
+  if (kt_begin < kt_end) {
+    load_k(kt_begin);
+    load_v(kt_begin);
+  }
+  for (int vt = kt_begin; vt < kt_end; vt += NW) {
+    const int key0 = kts.tile(vt) * KT;
+    f32x4 s[NH][2];
+#pragma unroll
+    for (int h = 0; h < NH; ++h) s[h][0] = s[h][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks)
+#pragma unroll
+      for (int h = 0; h < NH; ++h) s[h][ks & 1] = mma64(kf[ks][h], qf[ks], s[h][ks & 1], T());
+    const bool more = vt + NW < kt_end;
+    if (more) load_k(vt + NW);
+    float sc[NP];
+#pragma unroll
+    for (int h = 0; h < NH; ++h)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) sc[4 * h + e] = s[h][0][e] + s[h][1][e];
+    const bool inside = key0 + KT <= P || (key0 >= klo && key0 + KT <= khi);
+    if (!__all(inside)) {
+#pragma unroll
+      for (int e = 0; e < NP; ++e) {
+        const int key = key0 + NP * lg + e;
+        if (!(key < P || (key >= klo && key < khi))) sc[e] = -INFINITY;
+      }
+    }
+    float mt = sc[0];
+#pragma unroll
+    for (int e = 1; e < NP; ++e) mt = fmaxf(mt, sc[e]);
+    mt = max_xor16_32(mt) * sl2;
+    if (m_run == -INFINITY) m_run = mt;
+    if (__any(mt > m_run + kHeadroom)) {
+      const float m_new = mt > m_run + kHeadroom ? mt : m_run;
+      const float alpha = m_run == -INFINITY ? 0.f : exp2f(m_run - m_new);
+      l_run *= alpha;
+#pragma unroll
+      for (int dt = 0; dt < NDT; ++dt) acc[dt] *= alpha;
+      m_run = m_new;
+    }
+    const float m_use = m_run == -INFINITY ? 0.f : m_run;
+    float pr[NP];
+#pragma unroll
+    for (int e = 0; e < NP; ++e) {
+      pr[e] = __builtin_amdgcn_exp2f(fmaf(sc[e], sl2, -m_use));
+      l_run += pr[e];
+    }
+    u32x4 pf;
+    if constexpr (kBF16) {
+      u16x8 pb;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) pb[e] = f32_to_bf16(pr[e]);
+      pf = __builtin_bit_cast(u32x4, pb);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) pf[e] = __float_as_uint(pr[e]);
+    }
+#pragma unroll
+    for (int dt = 0; dt < NDT; ++dt) acc[dt] = mma64(vf[dt], pf, acc[dt], T());
+    if (more) load_v(vt + NW);
+  }
+  // merge: every wave's (m, l) of a row, then the weighted outputs, added in
+  // wave order
+  l_run = sum_xor16_32(l_run);
+  if (lg == 0) {
+    sml[wave][l16][0] = m_run;
+    sml[wave][l16][1] = l_run;
+  }
+  __syncthreads();
+  float M = -INFINITY;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) M = fmaxf(M, sml[w][l16][0]);
+  float den = 0.f;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) {
+    const float lw = sml[w][l16][1];
+    den += lw == 0.f ? 0.f : exp2f(sml[w][l16][0] - M) * lw;
+  }
+  // normalised; a split in which a row sees no key gives zeros and weight 0
+  const float scale = l_run == 0.f ? 0.f : exp2f(m_run - M) / den;
+  const size_t R = (size_t)a.B * a.tokens * a.n_q_heads;
+  if (a.n_split > 1 && threadIdx.x < 16 && tile0 + l16 < rows_bg) {
+    const size_t grow = (size_t)(b * a.tokens + tok) * a.n_q_heads + head;
+    *reinterpret_cast<f32x2*>(a.part_ml + ((size_t)split * R + grow) * 2) = f32x2{M, den};
+  }
+  float* so = few_so + (wave * 16 + l16) * LDO;
+#pragma unroll
+  for (int dt = 0; dt < NDT; ++dt)
+    *reinterpret_cast<f32x4*>(so + 16 * dt + 4 * lg) = acc[dt] * scale;
+  __syncthreads();
+  constexpr int PPR = DH / E;  // 16-byte output pieces per row
+  const int ldo = a.n_q_heads * DH;
+  for (int i = threadIdx.x; i < 16 * PPR; i += 64 * NW) {
+    const int r = i % 16, d = i / 16 * E;
+    if (tile0 + r >= rows_bg) continue;
+    f32x4 v[E / 4];
+#pragma unroll
+    for (int j = 0; j < E / 4; ++j) {
+      v[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int w = 0; w < NW; ++w)
+        v[j] += *reinterpret_cast<const f32x4*>(few_so + (w * 16 + r) * LDO + d + 4 * j);
+    }
+    const int t = (tile0 + r) / G, hd = g * G + (tile0 + r - t * G);
+    const int tr = b * a.tokens + t;
+    T* dst = a.n_split == 1
+                 ? reinterpret_cast<T*>(a.o) + tile_off<T>(tr, hd * DH + d, ldo)
+                 : reinterpret_cast<T*>(a.part_o) +
+                       ((size_t)split * R + (size_t)tr * a.n_q_heads + hd) * DH + d;
+#pragma unroll
+    for (int j = 0; j < E / 4; ++j) store4<T>(dst + 4 * j, v[j][0], v[j][1], v[j][2], v[j][3]);
+  }
+}
+
 // Merge of split partials in split order.  Partial z holds o_z = acc_z / l_z
 // (stored in the element type) with its reference m_z and sum l_z:
 // o = sum_z 2^(m_z - M) l_z o_z / sum_z 2^(m_z - M) l_z.  One wave per row; a
@@ -918,7 +1120,8 @@ __global__ __launch_bounds__(64 * NWV) void attn16d_kernel(AttnArgs a) {
 template <typename T, int DH>
 __global__ __launch_bounds__(256) void attn_combine(const T* __restrict__ part_o,
                                                     const float* __restrict__ part_ml,
-                                                    T* __restrict__ o, int R, int n_split) {
+                                                    T* __restrict__ o, int R, int n_split,
+                                                    int tiled_heads) {
   const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   if (row >= R) return;
@@ -962,7 +1165,10 @@ __global__ __launch_bounds__(256) void attn_combine(const T* __restrict__ part_o
     f32x4 num = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int z = 0; z < 8; ++z) num += mz[z] * pv[z][v];
-    store4<T>(o + (size_t)row * DH + d, num[0] * inv, num[1] * inv, num[2] * inv, num[3] * inv);
+    const int tr = tiled_heads ? row / tiled_heads : 0;
+    T* dst = tiled_heads ? o + tile_off<T>(tr, (row - tr * tiled_heads) * DH + d, tiled_heads * DH)
+                         : o + (size_t)row * DH + d;
+    store4<T>(dst, num[0] * inv, num[1] * inv, num[2] * inv, num[3] * inv);
   }
 }
 
@@ -971,9 +1177,14 @@ void launch_dh(const AttnArgs& a, hipStream_t s, int parts) {
   // 32-key tiles keep wide heads (and fp32) within the register file
   constexpr int KT = (sizeof(T) == 2 && DH < 192) ? 64 : 32;
   const int G = a.n_q_heads / a.n_kv_heads;
-  constexpr int RB = rows_per_block<T>();
-  dim3 grid((a.tokens * G + RB - 1) / RB, a.B * a.n_kv_heads, a.n_split);
-  if (parts & 1) {
+  if (few_rows(a.B * a.tokens)) {
+    if (parts & 1)
+      hipLaunchKernelGGL((attn_few_kernel<T, DH>),
+                         dim3((a.tokens * G + 15) / 16, a.B * a.n_kv_heads, a.n_split),
+                         dim3(64 * kFewAttnWaves), few_attn_lds<DH>(), s, a);
+  } else if (parts & 1) {
+    constexpr int RB = rows_per_block<T>();
+    dim3 grid((a.tokens * G + RB - 1) / RB, a.B * a.n_kv_heads, a.n_split);
     if constexpr (sizeof(T) == 2 && (DH == 128 || DH == 256))
       hipLaunchKernelGGL((attn16d_kernel<DH, kAttn16Waves, kAttnStages>), grid,
                          dim3(64 * kAttn16Waves), (attn16d_lds<DH>()), s, a);
@@ -986,7 +1197,8 @@ void launch_dh(const AttnArgs& a, hipStream_t s, int parts) {
     const int R = a.B * a.tokens * a.n_q_heads;
     hipLaunchKernelGGL((attn_combine<T, DH>), dim3((R + 3) / 4), dim3(256), 0, s,
                        reinterpret_cast<const T*>(a.part_o), a.part_ml,
-                       reinterpret_cast<T*>(a.o), R, a.n_split);
+                       reinterpret_cast<T*>(a.o), R, a.n_split,
+                       few_rows(a.B * a.tokens) ? a.n_q_heads : 0);
   }
 }
 
@@ -1032,16 +1244,33 @@ void launch_attention(const AttnArgs& a, hipStream_t s, int parts) {
   }
 }
 
-// The direct-load kernels' dynamic LDS exceeds the default limit.
-hipError_t attention_prepare() {
-  hipError_t e = hipFuncSetAttribute(
-      reinterpret_cast<const void*>(&attn16d_kernel<128, kAttn16Waves, kAttnStages>),
-      hipFuncAttributeMaxDynamicSharedMemorySize, attn16d_lds<128>());
-  if (e != hipSuccess) return e;
-  return hipFuncSetAttribute(
-      reinterpret_cast<const void*>(&attn16d_kernel<256, kAttn16Waves, kAttnStages>),
-      hipFuncAttributeMaxDynamicSharedMemorySize, attn16d_lds<256>());
+// Kernels whose dynamic LDS exceeds the default limit.
+template <typename F>
+static hipError_t allow_lds(F* kernel, int bytes) {
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                             hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
 }
+template <typename T, int DH>
+static hipError_t allow_few_lds() {
+  return allow_lds(&attn_few_kernel<T, DH>, few_attn_lds<DH>());
+}
+template <typename T>
+hipError_t attention_prepare() {
+  hipError_t e[6] = {allow_few_lds<T, 64>(),
+                     allow_few_lds<T, 128>(),
+                     allow_few_lds<T, 192>(),
+                     allow_few_lds<T, 256>(),
+                     hipSuccess, hipSuccess};
+  if constexpr (sizeof(T) == 2) {
+    e[4] = allow_lds(&attn16d_kernel<128, kAttn16Waves, kAttnStages>, attn16d_lds<128>());
+    e[5] = allow_lds(&attn16d_kernel<256, kAttn16Waves, kAttnStages>, attn16d_lds<256>());
+  }
+  for (hipError_t x : e)
+    if (x != hipSuccess) return x;
+  return hipSuccess;
+}
+template hipError_t attention_prepare<bf16_t>();
+template hipError_t attention_prepare<float>();
 
 template void launch_attention<bf16_t>(const AttnArgs&, hipStream_t, int);
 template void launch_attention<float>(const AttnArgs&, hipStream_t, int);

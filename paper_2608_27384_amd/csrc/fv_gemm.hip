@@ -207,28 +207,34 @@ __global__ __launch_bounds__(64 * NW * KG) void gemm_kernel(const T* __restrict_
     for (int j = 0; j < FN; ++j) acc[i][j] = f32x16{};
 
   // Thread piece p: 16 bytes of row r, k-vector c of a stage (A rows first).
+  // Consecutive threads take consecutive vectors of a row of A, consecutive
+  // rows of a weight tile.
   const T* gp[NP];
   int lp[NP];
 #pragma unroll
   for (int p = 0; p < NP; ++p) {
     const bool isa = p < NA;
     const int vi = tid + NT * (isa ? p : p - NA);
-    const int r = vi >> 3, c = vi & 7;
+    const int r = isa ? vi >> 3 : (vi >> 7) * 16 + (vi & 15);
+    const int c = isa ? vi & 7 : (vi >> 4) & 7;
     gp[p] = isa ? A + (size_t)min(m0 + r, M - 1) * K + c * EPV
-                : Bt + (size_t)(n0 + r) * K + c * EPV;
+                : Bt + tile_off<T>(n0 + r, c * EPV, K);
     lp[p] = (isa ? r : BM + r) * LDR + c * EPV;
   }
+
+  // offset of k for piece p: the weights' tiles put 16 rows' k side by side
+  auto koff = [](int p, int k) __attribute__((always_inline)) { return p < NA ? k : 16 * k; };
 
   // Prologue: stage kt0 into LDS buffer 0, stage kt0+1 into registers.
   u32x4 rg[NP];
 #pragma unroll
-  for (int p = 0; p < NP; ++p) rg[p] = *reinterpret_cast<const u32x4*>(gp[p] + kt0 * BK);
+  for (int p = 0; p < NP; ++p) rg[p] = *reinterpret_cast<const u32x4*>(gp[p] + koff(p, kt0 * BK));
 #pragma unroll
   for (int p = 0; p < NP; ++p) *reinterpret_cast<u32x4*>(&sm[lp[p]]) = rg[p];
   {
     const int k1 = min((kt0 + 1) * BK, klast);
 #pragma unroll
-    for (int p = 0; p < NP; ++p) rg[p] = *reinterpret_cast<const u32x4*>(gp[p] + k1);
+    for (int p = 0; p < NP; ++p) rg[p] = *reinterpret_cast<const u32x4*>(gp[p] + koff(p, k1));
   }
   __syncthreads();
 
@@ -275,7 +281,7 @@ __global__ __launch_bounds__(64 * NW * KG) void gemm_kernel(const T* __restrict_
       for (int p = 0; p < NP; ++p) {
         if (ks + 1 == NSG || (p * (NSG - 1)) / NP != ks) continue;
         *reinterpret_cast<u32x4*>(&nxt[lp[p]]) = rg[p];
-        rg[p] = *reinterpret_cast<const u32x4*>(gp[p] + knext);
+        rg[p] = *reinterpret_cast<const u32x4*>(gp[p] + koff(p, knext));
         ++nw;
       }
       // issue order: one fragment read after each MFMA, then one LDS store
@@ -368,9 +374,10 @@ constexpr bool epi_staged() { return EpiStaged<Epi>::value; }
 // BM x BN output tile per block of NW waves (WGM along M).  The A and W
 // k-tiles (64 k = 128 bytes per row) go from memory straight to LDS with the
 // direct-to-LDS loads (no staging registers, no LDS store instructions) into
-// a ring of NS stages; 16-byte piece c of stage row r sits at piece
+// a ring of NS stages; 16-byte piece c of A's stage row r sits at piece
 // c ^ ((r / 2) % 8), which keeps the MFMA fragment reads conflict-free
-// without padding.  One barrier per k-tile, after every wave's last fragment
+// without padding; W's tiles keep their layout, in which a fragment read is
+// runs of 256 bytes.  One barrier per k-tile, after every wave's last fragment
 // reads of the tile; the loads of tile k + NS are issued right after it into
 // the stage just consumed, so NS - 1 tiles are in flight while one is
 // multiplied.  Fragments of k-step s + LA are read during the MFMAs of
@@ -429,19 +436,22 @@ __global__ __launch_bounds__(64 * NW) void gemm_dma_kernel(const bf16_t* __restr
   const int nk_all = K / BK;
   const int kt0 = (kz * nk_all) / KS, kt1 = ((kz + 1) * nk_all) / KS;
 
-  // lane's piece of each of the wave's loads: 16-byte unit p of a stage
+  // lane's piece of each of the wave's loads (load L = NI wave + i of a
+  // stage): 8 rows of A, 128 bytes each, or one 1 KB weight tile (16 columns
+  // by 32 k; the two of a k-tile side by side), stored as it comes
   const bf16_t* src[NI];
 #pragma unroll
   for (int i = 0; i < NI; ++i) {
-    const int p = 64 * (NI * wave + i) + lane;
-    const int r = p >> 3, c = (p & 7) ^ ((r >> 1) & 7);
-    src[i] = r < BM ? A + (size_t)min(m0 + r, M - 1) * K + 8 * c
-                    : Bt + (size_t)(n0 + r - BM) * K + 8 * c;
+    const int L = NI * wave + i, r = 8 * L + (lane >> 3), c = (lane & 7) ^ ((r >> 1) & 7);
+    src[i] = L < BM / 8 ? A + (size_t)min(m0 + r, M - 1) * K + 8 * c
+                        : Bt + ((size_t)(n0 / 16 + (L - BM / 8) / 2) * (K / 32) + (L & 1)) * 512 +
+                              8 * lane;
   }
   auto issue = [&](int kt, int stage) __attribute__((always_inline)) {
     unsigned char* st = smem + stage * STAGE + 1024 * NI * wave;
 #pragma unroll
-    for (int i = 0; i < NI; ++i) lds_dma16(src[i] + (size_t)kt * BK, st + 1024 * i);
+    for (int i = 0; i < NI; ++i)
+      lds_dma16(src[i] + (size_t)kt * (NI * wave + i < BM / 8 ? BK : 1024), st + 1024 * i);
   };
 
   f32x16 acc[FM][FN];
@@ -451,7 +461,9 @@ __global__ __launch_bounds__(64 * NW) void gemm_dma_kernel(const bf16_t* __restr
     for (int j = 0; j < FN; ++j) acc[i][j] = f32x16{};
   const int lr = lane & 31, lg = lane >> 5;
   const int swz = (lr >> 1) & 7;  // rows 32 i + lr of any fragment share it
-  const int arow = wm * WTM, brow = BM + wn * WTN;
+  const int arow = wm * WTM;
+  // column lr of the wave's weight tiles: 16-column group, then column in it
+  const int bcol = BM * 64 + (wn * (WTN / 16) + (lr >> 4)) * 1024 + 8 * (lr & 15);
   // fragment slots: the k-step index within the tile when reading LA > 1
   // steps ahead, else alternate
   constexpr int NSL = LA == 1 ? 2 : NSTEP;
@@ -464,7 +476,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_dma_kernel(const bf16_t* __restr
       af[slot][i] = *reinterpret_cast<const u32x4*>(st + (arow + 32 * i + lr) * 64 + co);
 #pragma unroll
     for (int j = 0; j < FN; ++j)
-      bfr[slot][j] = *reinterpret_cast<const u32x4*>(st + (brow + 32 * j + lr) * 64 + co);
+      bfr[slot][j] = *reinterpret_cast<const u32x4*>(st + bcol + 2048 * j + 128 * (2 * ks + lg));
   };
 
 #pragma unroll
@@ -902,65 +914,14 @@ struct EpiGelu {
   }
 };
 
-// ------------------------------------------------------ few-row GEMM (GEMV)
-// out[m][n] = silu(sum_k A[m][k] W[n][k] + bias[n]) for M <= kGemvRows rows
-// (the time-MLP at small batch): one wave per output column n, lanes take
-// 16-byte pieces of k (the weight row once, every input row at the same
-// pieces), fp32 sums reduced across the wave.  One launch, no split-K pass.
-constexpr int kGemvRows = 16;
-template <typename T>
-__global__ __launch_bounds__(256) void gemv_bias_silu_kernel(const T* __restrict__ A,
-                                                             const T* __restrict__ Bt,
-                                                             const float* __restrict__ bias,
-                                                             T* __restrict__ out, int M, int N,
-                                                             int K, const int* __restrict__ skip) {
-  if (skip && *skip) return;
-  constexpr int EPV = 16 / (int)sizeof(T);  // elements per 16-byte piece
-  const int lane = threadIdx.x & 63;
-  const int n = blockIdx.x * 4 + (threadIdx.x >> 6);
-  float acc[kGemvRows];
-#pragma unroll
-  for (int m = 0; m < kGemvRows; ++m) acc[m] = 0.f;
-  const T* wrow = Bt + (size_t)n * K;
-  // rows m >= M re-read row M - 1 (in bounds, never stored), so every load
-  // is unconditional, and the scheduling barrier keeps all of a k-piece's
-  // loads ahead of its FMAs (left alone, the scheduler sinks each load next
-  // to its use and the wave waits for them one by one)
-#pragma unroll 1
-  for (int k0 = EPV * lane; k0 < K; k0 += 64 * EPV) {
-    const u32x4 wraw = *reinterpret_cast<const u32x4*>(wrow + k0);
-    u32x4 araw[kGemvRows];
-#pragma unroll
-    for (int m = 0; m < kGemvRows; ++m)
-      araw[m] = *reinterpret_cast<const u32x4*>(A + (size_t)min(m, M - 1) * K + k0);
-    __builtin_amdgcn_sched_barrier(0);
-    const T* we = reinterpret_cast<const T*>(&wraw);
-#pragma unroll
-    for (int m = 0; m < kGemvRows; ++m) {
-      const T* e = reinterpret_cast<const T*>(&araw[m]);
-#pragma unroll
-      for (int i = 0; i < EPV; ++i) acc[m] = fmaf(to_f32(e[i]), to_f32(we[i]), acc[m]);
-    }
-  }
-  const float b = bias[n];
-#pragma unroll
-  for (int m = 0; m < kGemvRows; ++m) {
-    const float v = wave_sum(acc[m]);
-    if (m < M && lane == 0) out[(size_t)m * N + n] = from_f32<T>(silu_f(v + b));
-  }
-}
-
 // ------------------------------------------ few-row GEMM, weights streamed
 // out[m][n] = sum_k A[m][k] W[n][k] + bias[n] in fp32, bf16 operands, for
 // M <= 16 rows and a weight matrix far larger than the memory-side cache
 // (the FiLM maps of every norm at small batch), so the kernel is a stream of
 // the weights at HBM rate.  A wave owns 16 output columns at a time, whose
-// weight rows are one contiguous range, and multiplies them with MFMA
-// 16x16x32 tiles.  Lane (q, c) = (lane / 16, lane % 16) takes column c and,
-// of every 128-element k batch, the 64 contiguous bytes at k = 32q: four
-// 16-byte pieces, piece s holding k = 32q + 8s .. +8.  The MFMA's k order is
-// permuted that way on both operands, so every lane's weight loads are
-// contiguous; A, permuted once, stays in registers.  The weight pieces of
+// weight tiles are one contiguous range, and multiplies them with MFMA
+// 16x16x32 tiles: a 128-element k batch is four tiles, each one contiguous
+// 1 KB load.  A stays in registers.  The weight pieces of
 // the next three batches (across the end of a column group, the next
 // group's first three) are in flight while one batch is multiplied.
 constexpr int kStreamRows = 16;
@@ -980,19 +941,19 @@ __global__ __launch_bounds__(256) void stream_bias_f32_kernel(const bf16_t* __re
   // rows m >= M repeat row M - 1: every load is in bounds and unconditional,
   // and those rows are never stored
   bf16x8 a[NB][4];
-  const bf16_t* arow = A + (size_t)min(c, M - 1) * K + 32 * q;
+  const bf16_t* arow = A + (size_t)min(c, M - 1) * K + 8 * q;
 #pragma unroll
   for (int b = 0; b < NB; ++b)
 #pragma unroll
     for (int p = 0; p < 4; ++p)
-      a[b][p] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u16x8*>(arow + 128 * b + 8 * p));
-  auto wrow = [&](int gg) { return Bt + (size_t)(16 * gg + c) * K + 32 * q; };
+      a[b][p] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u16x8*>(arow + 128 * b + 32 * p));
+  auto wrow = [&](int gg) { return Bt + (size_t)16 * gg * K + 8 * lane; };
   const bf16_t* cur = wrow(g);
   u16x8 w[R][4];
 #pragma unroll
   for (int b = 0; b < AHEAD; ++b)
 #pragma unroll
-    for (int p = 0; p < 4; ++p) w[b][p] = *reinterpret_cast<const u16x8*>(cur + 128 * b + 8 * p);
+    for (int p = 0; p < 4; ++p) w[b][p] = *reinterpret_cast<const u16x8*>(cur + 2048 * b + 512 * p);
   for (;;) {
     // the last group's look-ahead re-reads its own first batches (cache
     // hits) instead of another group's weights
@@ -1001,9 +962,9 @@ __global__ __launch_bounds__(256) void stream_bias_f32_kernel(const bf16_t* __re
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
       const int ib = b + AHEAD;
-      const bf16_t* src = ib < NB ? cur + 128 * ib : nxt + 128 * (ib - NB);
+      const bf16_t* src = ib < NB ? cur + 2048 * ib : nxt + 2048 * (ib - NB);
 #pragma unroll
-      for (int p = 0; p < 4; ++p) w[ib % R][p] = *reinterpret_cast<const u16x8*>(src + 8 * p);
+      for (int p = 0; p < 4; ++p) w[ib % R][p] = *reinterpret_cast<const u16x8*>(src + 512 * p);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int p = 0; p < 4; ++p)
@@ -1038,7 +999,8 @@ void launch_stream_bias_f32(const bf16_t* A, const bf16_t* Bt, const float* bias
 // Tile shapes (BM x BN, waves); every wave owns a sub-tile at least 64
 // columns wide, so paired epilogues find both partners of a 64-column pair
 // group in one wave.
-enum Tile { T256x128w8 = 0, T128x128w8 = 1, T64x128w4 = 2, T32x128w2 = 3, T256x256big = 4 };
+enum Tile { T256x128w8 = 0, T128x128w8 = 1, T64x128w4 = 2, T32x128w2 = 3, T256x256big = 4,
+            TFew = 5 };
 constexpr int kTileBM[] = {256, 128, 64, 32, 256};
 constexpr int kTileBN[] = {128, 128, 128, 128, 256};
 // k-groups per tile (waves per block = NW x KG): the 2-wave 32-row tile
@@ -1138,6 +1100,17 @@ void run_gemm(const T* A, const T* Bt, int M, int N, int K, const GemmWork& w, c
 // projections, whose split sum is fused into the next kernel at no extra
 // launch) grids of up to 160 tiles are split too.
 GemmPlan plan_gemm(int M, int N, int K, bool bf16, bool reduce_fused) {
+  if (N % 128 == 0 && M > 0 && few_rows(M)) {
+    GemmPlan p;
+    p.tile = TFew;
+    p.ks = reduce_fused ? few_splits(N, K, bf16 ? 2 : 4) : 1;
+    p.tiles = N / 16;
+    p.ws_floats = reduce_fused ? (size_t)p.ks * M * N : 0;
+    return p;
+  }
+  return plan_tiles(M, N, K, bf16, reduce_fused);
+}
+GemmPlan plan_tiles(int M, int N, int K, bool bf16, bool reduce_fused) {
   GemmPlan p;
   if (N % 128 || M <= 0) return p;
   const int bk = bf16 ? 64 : 32, nk = K / bk;
@@ -1189,6 +1162,10 @@ int gemm_partials(const T* A, const T* Bt, int M, int N, int K, const GemmWork& 
                   hipStream_t s, bool* bf16_parts) {
   const GemmPlan p = plan_gemm(M, N, K, sizeof(T) == 2, true);
   *bf16_parts = false;
+  if (p.tile == TFew) {
+    few_partials(A, Bt, w.ws, M, N, K, p.ks, s);
+    return p.ks;
+  }
   if (p.ks <= 1) return 1;
   if constexpr (sizeof(T) == 2) {
     if (try_dma(A, Bt, M, N, K, p, w, EpiNone{}, s)) {
@@ -1208,11 +1185,7 @@ int gemm_partials(const T* A, const T* Bt, int M, int N, int K, const GemmWork& 
 template <typename T>
 void gemm_bias_silu(const T* A, const T* Bt, const float* bias, T* out, int M, int N, int K,
                     const GemmWork& w, hipStream_t s, const int* skip) {
-  if (M <= kGemvRows && N % 4 == 0 && K % (16 / (int)sizeof(T)) == 0) {
-    hipLaunchKernelGGL((gemv_bias_silu_kernel<T>), dim3(N / 4), dim3(256), 0, s, A, Bt, bias, out,
-                       M, N, K, skip);
-    return;
-  }
+  if (few_rows(M)) return few_bias_silu(A, Bt, bias, out, M, N, K, s, skip);
   run_gemm(A, Bt, M, N, K, w, EpiBiasSilu<T>{out, bias, N, skip}, s);
 }
 template <typename T>
@@ -1227,11 +1200,13 @@ void gemm_bias_f32(const T* A, const T* Bt, const float* bias, float* out, int M
       }
     }
   }
+  if (few_rows(M)) return few_bias_f32(A, Bt, bias, out, M, N, K, s, skip);
   run_gemm(A, Bt, M, N, K, w, EpiBiasF32{out, bias, N, skip}, s);
 }
 template <typename T>
 void gemm_qkv(const T* A, const T* Bt, const QkvArgs<T>& qa, int M, int N, int K,
               const GemmWork& w, hipStream_t s) {
+  if (few_rows(M)) return few_qkv(A, Bt, qa, M, N, K, s);
   run_gemm(A, Bt, M, N, K, w, EpiQkv<T>{qa}, s);
 }
 template <typename T>
@@ -1243,11 +1218,13 @@ void gemm_gated_resid(const T* A, const T* Bt, float* h, const float* mod, int m
 template <typename T>
 void gemm_geglu(const T* A, const T* Bt, T* out, int M, int N, int K, const GemmWork& w,
                 hipStream_t s) {
+  if (few_rows(M)) return few_geglu(A, Bt, out, M, N, K, s);
   run_gemm(A, Bt, M, N, K, w, EpiGeglu<T>{out, N / 2}, s);
 }
 template <typename T>
 void gemm_gelu(const T* A, const T* Bt, T* out, int M, int N, int K, const GemmWork& w,
                hipStream_t s) {
+  if (few_rows(M)) return few_gelu(A, Bt, out, M, N, K, s);
   run_gemm(A, Bt, M, N, K, w, EpiGelu<T>{out, N}, s);
 }
 

@@ -63,6 +63,20 @@ template <> struct Mfma<float> {
   }
 };
 
+// A 16x16 product over one 64-byte k block (see tile_off), both operands as
+// 16-byte pieces.
+__device__ __forceinline__ f32x4 mma64(u32x4 x, u32x4 y, f32x4 c, bf16_t) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, x),
+                                                 __builtin_bit_cast(bf16x8, y), c, 0, 0, 0);
+}
+__device__ __forceinline__ f32x4 mma64(u32x4 x, u32x4 y, f32x4 c, float) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+    c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(x[e]), __uint_as_float(y[e]), c, 0, 0,
+                                             0);
+  return c;
+}
+
 // Four consecutive elements as fp32 (16-byte fp32 or 8-byte bf16 load; p aligned to that).
 __device__ __forceinline__ f32x4 load4_f32(const float* p) { return *reinterpret_cast<const f32x4*>(p); }
 __device__ __forceinline__ f32x4 load4_f32(const bf16_t* p) {
@@ -79,6 +93,20 @@ __device__ __forceinline__ void store4<float>(float* p, float a, float b, float 
 template <>
 __device__ __forceinline__ void store4<bf16_t>(bf16_t* p, float a, float b, float c, float d) {
   *reinterpret_cast<u16x4*>(p) = u16x4{f32_to_bf16(a), f32_to_bf16(b), f32_to_bf16(c), f32_to_bf16(d)};
+}
+
+// Tiled operand layout: a matrix [rows][K] in tiles of 16 rows by 64 bytes of
+// k, each tile one contiguous 1 KB run in MFMA fragment order (lane (q, c) =
+// piece q of row c), the tiles of a 16-row group following each other along
+// k.  tile_off is the element offset of (row, k).  Every weight is stored
+// this way (a fragment load is one contiguous 1 KB run; a 64-row k-tile of a
+// direct-to-LDS load is runs of 2 KB instead of 128-byte rows K apart), and
+// so are the activations between the kernels of a few-row pass.
+template <typename T>
+__host__ __device__ __forceinline__ size_t tile_off(int row, int k, int K) {
+  constexpr int E = 16 / (int)sizeof(T);  // elements per 16-byte piece
+  return ((size_t)(row >> 4) * (K / (4 * E)) + k / (4 * E)) * (64 * E) +
+         (k % (4 * E)) / E * (16 * E) + (row & 15) * E + k % E;
 }
 
 // Sum over the 64 lanes, the same value in every lane, without LDS
@@ -152,8 +180,8 @@ __device__ __forceinline__ float gelu_tanh_f(float x) {
 
 // ------------------------------------------------------------ GEMM launches
 // C[M][N] = A[M][K] * Bt[N][K]^T with fp32 accumulation, followed by a fused
-// epilogue.  A is row-major with leading dimension K; Bt is the weight stored
-// output-major ([out][in]).  Requirements: N % 128 == 0, K % 64 == 0 (bf16) or
+// epilogue.  A is row-major with leading dimension K (tiled in a few-row
+// pass); Bt is the weight stored output-major ([out][in]) in the tiled layout.  Requirements: N % 128 == 0, K % 64 == 0 (bf16) or
 // K % 32 == 0 (fp32), 16-byte aligned base pointers.
 struct GemmPlan {
   int tile = -1, ks = 1, tiles = 0;  // tile shape id, split-K factor, output tiles
@@ -162,6 +190,8 @@ struct GemmPlan {
 // reduce_fused: the plan of an output or down projection (its split sum
 // runs inside the next kernel, so splitting costs no launch).
 GemmPlan plan_gemm(int M, int N, int K, bool bf16, bool reduce_fused = false);
+// The tile kernels' plan alone (what plan_gemm gives above kFewRows rows).
+GemmPlan plan_tiles(int M, int N, int K, bool bf16, bool reduce_fused = false);
 
 // Split-K scratch shared by every GEMM of a handle (launches are stream
 // ordered): partial tiles, fp32, or bf16 for the direct-to-LDS kernel with
@@ -217,6 +247,28 @@ template <typename T>
 int gemm_partials(const T* A, const T* Bt, int M, int N, int K, const GemmWork& w,
                   hipStream_t s, bool* bf16_parts);
 
+// Few-row GEMMs (fv_few.hip), M <= kFewRows: one pass, no split-K workspace
+// except the projections' k slices, which the fused residual reduction adds.
+// A forward pass of at most kFewRows token rows keeps its activations u, o
+// and m in the tiled layout; the time-MLP's (few_bias_*) are row-major.
+constexpr int kFewRows = 64;
+__host__ __device__ __forceinline__ bool few_rows(int M) { return M <= kFewRows; }
+int few_splits(int N, int K, int esz);
+template <typename T>
+void few_partials(const T* A, const T* Bt, float* ws, int M, int N, int K, int ks, hipStream_t s);
+template <typename T>
+void few_bias_silu(const T* A, const T* Bt, const float* bias, T* out, int M, int N, int K,
+                   hipStream_t s, const int* skip);
+template <typename T>
+void few_bias_f32(const T* A, const T* Bt, const float* bias, float* out, int M, int N, int K,
+                  hipStream_t s, const int* skip);
+template <typename T>
+void few_qkv(const T* A, const T* Bt, const QkvArgs<T>& qa, int M, int N, int K, hipStream_t s);
+template <typename T>
+void few_geglu(const T* A, const T* Bt, T* out, int M, int N, int K, hipStream_t s);
+template <typename T>
+void few_gelu(const T* A, const T* Bt, T* out, int M, int N, int K, hipStream_t s);
+
 // ------------------------------------------------------------ other kernels
 // FiLM maps shared across streams.  Chunk row cr (stream b, slot k, cr =
 // b K + k) normally reads its own row of the FiLM maps.  When every stream's
@@ -235,12 +287,13 @@ void launch_time_embed(const float* t, T* e, int rows, int width, hipStream_t s,
                        int* period = nullptr, int K = 0);
 // xs (optional, only where head_fusable): a copy of x for the fused Euler
 // update of launch_final_euler.  `period` (here and below): the FiLM-row
-// sharing flag described above, or nullptr.
+// sharing flag described above, or nullptr.  tiled (here and below): u goes
+// out in the tiled layout.
 template <typename T>
 void launch_embed_adarms(const float* x, const float* w_in, const float* b_in, float* h,
                          const float* mod, int mod_ld, int chunk_len, float eps, T* u, int rows,
                          int A, int W, hipStream_t s, float* xs = nullptr,
-                         const int* period = nullptr);
+                         const int* period = nullptr, bool tiled = false);
 // h += gate * sum_z part[z] (split order); then, if norm_off >= 0,
 // u = rmsnorm(h) (1 + scale) + shift with the modulation at norm_off.
 // part holds bf16 values when bf16_parts, else fp32.  [pf, pf + pf_bytes)
@@ -250,7 +303,7 @@ template <typename T>
 void launch_resid_norm(const void* part, bool bf16_parts, int ks, float* h, const float* mod,
                        int mod_ld, int gate_off, int norm_off, int chunk_len, float eps, T* u,
                        int rows, int W, const void* pf, size_t pf_bytes, hipStream_t s,
-                       const int* period = nullptr);
+                       const int* period = nullptr, bool tiled = false);
 template <typename T>
 void launch_adarms(const float* h, const float* mod, int mod_ld, int scale_off, int chunk_len,
                    float eps, T* u, int rows, int W, hipStream_t s, const int* period = nullptr);
@@ -335,13 +388,15 @@ __host__ __device__ __forceinline__ void visible_chunks(int kq, int K, int first
     hi = K;
   }
 }
-// parts: bit 0 launches the score/value kernel, bit 1 the split combine.
+// parts: bit 0 launches the score/value kernel, bit 1 the split combine.  A
+// few-row pass (B * tokens <= kFewRows) leaves o in the tiled layout.
 template <typename T>
 void launch_attention(const AttnArgs& a, hipStream_t s, int parts = 3);
 template <typename T>
 int attention_row_tiles(int tokens, int n_q_heads, int n_kv_heads);
-// Raises the dynamic LDS limit of the direct-load attention kernels (call
+// Raises the dynamic LDS limit of the attention kernels that need it (call
 // once per device before the first launch).
+template <typename T>
 hipError_t attention_prepare();
 
 // ------------------------------------------------------------------- handle

@@ -62,7 +62,8 @@ template <typename T, int NC>
 __global__ __launch_bounds__(256) void embed_adarms_kernel(
     const float* __restrict__ x, const float* __restrict__ w_in, const float* __restrict__ b_in,
     float* __restrict__ h, const float* __restrict__ mod, int mod_ld, int chunk_len, float eps,
-    T* __restrict__ u, int rows, int A, int W, const int* __restrict__ period) {
+    T* __restrict__ u, int rows, int A, int W, const int* __restrict__ period,
+    bool tiled) {
   // thread t owns columns 4t + 1024 i (i < NC, W <= 1024 NC) of kEmbRows
   // rows; the modulation and the first weight batch are requested before
   // anything waits, and h stays in registers between the embedding and the
@@ -144,7 +145,8 @@ __global__ __launch_bounds__(256) void embed_adarms_kernel(
       const int c = 4 * tid + 1024 * i;
       if (c >= W) continue;
       const f32x4 hv = acc[i][r];
-      store4<T>(u + (size_t)row * W + c, hv[0] * rinv * (1.0f + sv[i][r][0]) + bv[i][r][0],
+      store4<T>(u + (tiled ? tile_off<T>(row, c, W) : (size_t)row * W + c),
+              hv[0] * rinv * (1.0f + sv[i][r][0]) + bv[i][r][0],
                 hv[1] * rinv * (1.0f + sv[i][r][1]) + bv[i][r][1],
                 hv[2] * rinv * (1.0f + sv[i][r][2]) + bv[i][r][2],
                 hv[3] * rinv * (1.0f + sv[i][r][3]) + bv[i][r][3]);
@@ -163,7 +165,7 @@ __global__ __launch_bounds__(256) void embed_adarms_small_kernel(
     const float* __restrict__ x, const float* __restrict__ w_in, const float* __restrict__ b_in,
     float* __restrict__ h, const float* __restrict__ mod, int mod_ld, int chunk_len, float eps,
     T* __restrict__ u, int rows, int A, int W, float* __restrict__ xs,
-    const int* __restrict__ period) {
+    const int* __restrict__ period, bool tiled) {
   constexpr int R = kEmbSmallRows, AM = 32;
   __shared__ float sred[R][4];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -211,7 +213,8 @@ __global__ __launch_bounds__(256) void embed_adarms_small_kernel(
     if (row >= rows || !own) continue;
     const float tot = sred[r][0] + sred[r][1] + sred[r][2] + sred[r][3];
     const float rinv = 1.0f / sqrtf(tot / (float)W + eps);
-    store4<T>(u + (size_t)row * W + c, acc[r][0] * rinv * (1.0f + sv[r][0]) + bv[r][0],
+    store4<T>(u + (tiled ? tile_off<T>(row, c, W) : (size_t)row * W + c),
+              acc[r][0] * rinv * (1.0f + sv[r][0]) + bv[r][0],
               acc[r][1] * rinv * (1.0f + sv[r][1]) + bv[r][1],
               acc[r][2] * rinv * (1.0f + sv[r][2]) + bv[r][2],
               acc[r][3] * rinv * (1.0f + sv[r][3]) + bv[r][3]);
@@ -344,7 +347,8 @@ __global__ __launch_bounds__(256) void resid_norm_kernel(const P* __restrict__ p
                                                          int chunk_len, float eps,
                                                          T* __restrict__ u, int rows, int W,
                                                          const void* pf, size_t pf_bytes,
-                                                         const int* __restrict__ period) {
+                                                         const int* __restrict__ period,
+                                                         bool tiled) {
   __shared__ float red[4];
   const int row = blockIdx.x, tid = threadIdx.x;
   const float* mrow = mod + (size_t)film_row(row / chunk_len, film_period(period)) * mod_ld;
@@ -389,7 +393,8 @@ __global__ __launch_bounds__(256) void resid_norm_kernel(const P* __restrict__ p
   for (int q = 0; q < NQ; ++q) {
     if (col[q] < W) {
       const f32x4 sv = svq[q], bv = bvq[q], x = hv[q];
-      store4<T>(u + (size_t)row * W + col[q], x[0] * rinv * (1.0f + sv[0]) + bv[0],
+      store4<T>(u + (tiled ? tile_off<T>(row, col[q], W) : (size_t)row * W + col[q]),
+                x[0] * rinv * (1.0f + sv[0]) + bv[0],
                 x[1] * rinv * (1.0f + sv[1]) + bv[1], x[2] * rinv * (1.0f + sv[2]) + bv[2],
                 x[3] * rinv * (1.0f + sv[3]) + bv[3]);
     }
@@ -999,7 +1004,8 @@ bool head_fusable(int rows, int W, int A) {
 template <typename T>
 void launch_embed_adarms(const float* x, const float* w_in, const float* b_in, float* h,
                          const float* mod, int mod_ld, int chunk_len, float eps, T* u, int rows,
-                         int A, int W, hipStream_t s, float* xs, const int* period) {
+                         int A, int W, hipStream_t s, float* xs, const int* period,
+                         bool tiled) {
   if (rows >= kManyRows && W <= 1024 && A <= 32) {
     // one round of one workgroup per CU
     const int rpb = kEmbRows * ((rows + kEmbRows * 256 - 1) / (kEmbRows * 256));
@@ -1010,29 +1016,29 @@ void launch_embed_adarms(const float* x, const float* w_in, const float* b_in, f
   if (W <= 1024 && W % 4 == 0 && A <= 32) {
     hipLaunchKernelGGL((embed_adarms_small_kernel<T>), dim3((rows + kEmbSmallRows - 1) / kEmbSmallRows),
                        dim3(256), 0, s, x, w_in, b_in, h, mod, mod_ld, chunk_len, eps, u, rows, A, W,
-                       xs, period);
+                       xs, period, tiled);
     return;
   }
   const dim3 grid((rows + kEmbRows - 1) / kEmbRows);
   if (W <= 1024)
     hipLaunchKernelGGL((embed_adarms_kernel<T, 1>), grid, dim3(256), 0, s, x, w_in, b_in, h, mod,
-                       mod_ld, chunk_len, eps, u, rows, A, W, period);
+                       mod_ld, chunk_len, eps, u, rows, A, W, period, tiled);
   else
     hipLaunchKernelGGL((embed_adarms_kernel<T, 2>), grid, dim3(256), 0, s, x, w_in, b_in, h, mod,
-                       mod_ld, chunk_len, eps, u, rows, A, W, period);
+                       mod_ld, chunk_len, eps, u, rows, A, W, period, tiled);
 }
 
 template <typename T>
 void launch_resid_norm(const void* part, bool bf16_parts, int ks, float* h, const float* mod,
                        int mod_ld, int gate_off, int norm_off, int chunk_len, float eps, T* u,
                        int rows, int W, const void* pf, size_t pf_bytes, hipStream_t s,
-                       const int* period) {
+                       const int* period, bool tiled) {
   // split slots (power of two >= ks, at most 8) and column groups per thread
   const int ksm = ks <= 2 ? 2 : ks <= 4 ? 4 : 8;
   const int nq = W <= 1024 ? 1 : 2;
   auto go = [&](auto kern, const auto* pp) {
     hipLaunchKernelGGL(kern, dim3(rows), dim3(256), 0, s, pp, ks, h, mod, mod_ld, gate_off,
-                       norm_off, chunk_len, eps, u, rows, W, pf, pf_bytes, period);
+                       norm_off, chunk_len, eps, u, rows, W, pf, pf_bytes, period, tiled);
   };
 #define FV_RN(P, KSM, NQ) go(resid_norm_kernel<T, P, KSM, NQ>, static_cast<const P*>(part))
 #define FV_RN_Q(P, KSM) (nq == 1 ? FV_RN(P, KSM, 1) : FV_RN(P, KSM, 2))
@@ -1126,16 +1132,16 @@ template void launch_time_embed<bf16_t>(const float*, bf16_t*, int, int, hipStre
 template void launch_time_embed<float>(const float*, float*, int, int, hipStream_t, int*, int);
 template void launch_embed_adarms<bf16_t>(const float*, const float*, const float*, float*,
                                           const float*, int, int, float, bf16_t*, int, int, int,
-                                          hipStream_t, float*, const int*);
+                                          hipStream_t, float*, const int*, bool);
 template void launch_embed_adarms<float>(const float*, const float*, const float*, float*,
                                          const float*, int, int, float, float*, int, int, int,
-                                         hipStream_t, float*, const int*);
+                                         hipStream_t, float*, const int*, bool);
 template void launch_resid_norm<bf16_t>(const void*, bool, int, float*, const float*, int, int,
                                         int, int, float, bf16_t*, int, int, const void*, size_t,
-                                        hipStream_t, const int*);
+                                        hipStream_t, const int*, bool);
 template void launch_resid_norm<float>(const void*, bool, int, float*, const float*, int, int,
                                        int, int, float, float*, int, int, const void*, size_t,
-                                       hipStream_t, const int*);
+                                       hipStream_t, const int*, bool);
 template void launch_adarms<bf16_t>(const float*, const float*, int, int, int, float, bf16_t*,
                                     int, int, hipStream_t, const int*);
 template void launch_adarms<float>(const float*, const float*, int, int, int, float, float*, int,

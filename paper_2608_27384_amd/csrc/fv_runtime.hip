@@ -93,17 +93,26 @@ void* dalloc(Handle* h, size_t bytes) {
   return p;
 }
 
-// Uploads host fp32 values as the handle's storage type (bf16 RNE or fp32).
-void* upload_T(Handle* h, const std::vector<float>& v) {
-  void* d = dalloc(h, v.size() * h->esz);
-  if (h->bf16) {
-    std::vector<uint16_t> b(v.size());
-    for (size_t i = 0; i < v.size(); ++i) b[i] = host_bf16(v[i]);
-    FV_HIP(hipMemcpy(d, b.data(), b.size() * 2, hipMemcpyHostToDevice));
-  } else {
-    FV_HIP(hipMemcpy(d, v.data(), v.size() * 4, hipMemcpyHostToDevice));
-  }
+// Uploads a weight, host fp32 [rows][K] (rows a multiple of 16), as the
+// handle's storage type (bf16 RNE or fp32) in the tiled layout of tile_off.
+template <typename T, typename Conv>
+void* upload_tiled(Handle* h, const std::vector<float>& v, int K, Conv conv) {
+  constexpr int E = 16 / (int)sizeof(T);
+  std::vector<T> b(v.size());
+  const int rows = (int)(v.size() / K);
+  for (int r = 0; r < rows; ++r)
+    for (int k = 0; k < K; k += E) {
+      const float* src = v.data() + (size_t)r * K + k;
+      T* dst = b.data() + tile_off<T>(r, k, K);
+      for (int e = 0; e < E; ++e) dst[e] = conv(src[e]);
+    }
+  void* d = dalloc(h, b.size() * sizeof(T));
+  FV_HIP(hipMemcpy(d, b.data(), b.size() * sizeof(T), hipMemcpyHostToDevice));
   return d;
+}
+void* upload_T(Handle* h, const std::vector<float>& v, int K) {
+  if (h->bf16) return upload_tiled<uint16_t>(h, v, K, host_bf16);
+  return upload_tiled<float>(h, v, K, [](float x) { return x; });
 }
 
 // fp32 upload; in bf16 mode values are first rounded to bf16 (stored as fp32).
@@ -158,15 +167,16 @@ void validate_cfg(const fv_cfg& c) {
   if (!(c.rope_theta > 0.f) || !std::isfinite(c.rope_theta)) bad("rope_theta must be > 0");
 }
 
-// Key splits per attention row tile: enough blocks for two per CU (about 512),
-// at most 8 splits.
-int attn_split(const Handle* h, int B) {
+// Key splits per attention row tile: enough for about `blocks` workgroups, at
+// most 8 splits.
+int attn_split_for(const Handle* h, int B, int blocks) {
   const int tiles = h->bf16 ? attention_row_tiles<bf16_t>(h->T, h->Hq, h->Hkv)
                             : attention_row_tiles<float>(h->T, h->Hq, h->Hkv);
   const int base = tiles * B * h->Hkv;
-  int s = (512 + base - 1) / base;
+  const int s = (blocks + base - 1) / base;
   return s < 1 ? 1 : (s > 8 ? 8 : s);
 }
+int attn_split(const Handle* h, int B) { return attn_split_for(h, B, 512); }
 
 // ------------------------------------------------------------------ forward
 // Output projection / down projection with the gated residual, fused with
@@ -186,7 +196,7 @@ void resid_block(Handle* h, const float* mod, const int* per, const T* A, const 
   if (ks > 1) {
     launch_resid_norm<T>(h->gw.ws, bf16_parts, ks, h->hres, mod, h->Nmod, gate_off, norm_off,
                          h->C, h->cfg.rms_eps, (T*)h->u, rowsT, W,
-                         next_w, next_bytes, s, per);
+                         next_w, next_bytes, s, per, few_rows(rowsT));
   } else {
     if (norm_off >= 0)
       launch_adarms<T>(h->hres, mod, h->Nmod, norm_off, h->C, h->cfg.rms_eps, (T*)h->u, rowsT,
@@ -260,7 +270,7 @@ bool enqueue_forward(Handle* h, const float* buffer, const float* t, int B, floa
   }
   h->film_per = mod_cached ? nullptr : per;  // the flag that goes with h->mod (debug stages)
   launch_embed_adarms<T>(buffer, h->w_in, h->b_in, h->hres, mod, Nmod, h->C, h->cfg.rms_eps,
-                         (T*)h->u, rowsT, h->A, W, s, fuse ? h->v : nullptr, per);
+                         (T*)h->u, rowsT, h->A, W, s, fuse ? h->v : nullptr, per, few_rows(rowsT));
   const int n_split = attn_split(h, B);
   for (int l = 0; l < n_layers_run; ++l) {
     T* kar = (T*)h->karena + l * layer_elems;
@@ -275,7 +285,9 @@ bool enqueue_forward(Handle* h, const float* buffer, const float* t, int B, floa
                                   (size_t)W * h->Hq * h->dh * h->esz);
     launch_attention<T>(aa, s);
     // (no prefetch of the gate/up weights here: the reduction would wait
-    // for 16.8 MB of loads, batch-1 step 1433 -> 1415 us without it)
+    // for 16.8 MB of loads, batch-1 step 1433 -> 1415 us without it; none of
+    // the next QKV weights in a few-row pass, whose reduction is too short to
+    // hide it: 50 rows, 18 layers, 875 -> 867 us without it)
     resid_block<T>(h, mod, per, (const T*)h->o, (const T*)h->wo[l], h->Hq * h->dh,
                    n_attn * 3 * W + 2 * W, n_mlp * 3 * W, rowsT, s);
     if (h->cfg.mlp_gated)
@@ -285,7 +297,8 @@ bool enqueue_forward(Handle* h, const float* buffer, const float* t, int B, floa
     const int next_norm = l + 1 < h->L ? 2 * (l + 1) * 3 * W : -1;
     resid_block<T>(h, mod, per, (const T*)h->m, (const T*)h->wd[l], h->F,
                    n_mlp * 3 * W + 2 * W, next_norm, rowsT, s,
-                   l + 1 < h->L ? h->wqkv[l + 1] : nullptr, (size_t)h->Nqkv * W * h->esz);
+                   l + 1 < h->L && !few_rows(rowsT) ? h->wqkv[l + 1] : nullptr,
+                   (size_t)h->Nqkv * W * h->esz);
   }
   if (fuse) {
     EulerDest d = *eu;
@@ -322,7 +335,7 @@ void proj_norm_only(Handle* h, int K, int gate_off, int norm_off, int rowsT, hip
   if (p.ks > 1)
     launch_resid_norm<T>(h->gw.ws, gemm_partials_bf16(p, h->bf16), p.ks, h->hres, h->mod, h->Nmod,
                          gate_off, norm_off, h->C, h->cfg.rms_eps, (T*)h->u, rowsT, h->W,
-                         pf, pf_bytes, s, h->film_per);
+                         pf, pf_bytes, s, h->film_per, few_rows(rowsT));
   else if (norm_off >= 0)
     launch_adarms<T>(h->hres, h->mod, h->Nmod, norm_off, h->C, h->cfg.rms_eps, (T*)h->u, rowsT,
                      h->W, s, h->film_per);
@@ -541,20 +554,30 @@ struct StepScratch {
   size_t part_o = 0, part_ml = 0, ws = 0;
   size_t total() const { return part_o + part_ml + ws; }
 };
-StepScratch step_scratch(const Handle* h, int B) {
+template <typename Plan>
+StepScratch scratch_of(const Handle* h, int B, int s, Plan plan) {
   StepScratch r;
-  const int s = attn_split(h, B);
   if (s > 1) {
     const size_t rows = (size_t)s * B * h->T * h->Hq;
     r.part_o = round256(rows * h->dh * h->esz);
     r.part_ml = round256(rows * 2 * 4);
   }
   const int W = h->W, rk = B * h->K, rt = B * h->T, qd = h->Hq * h->dh;
-  const GemmPlan ps[] = {plan_gemm(rk, W, W, h->bf16), plan_gemm(rk, h->Nmod, W, h->bf16),
-                         plan_gemm(rt, h->Nqkv, W, h->bf16), plan_gemm(rt, W, qd, h->bf16, true),
-                         plan_gemm(rt, h->Ngu, W, h->bf16), plan_gemm(rt, W, h->F, h->bf16, true)};
+  const GemmPlan ps[] = {plan(rk, W, W, h->bf16, false),       plan(rk, h->Nmod, W, h->bf16, false),
+                         plan(rt, h->Nqkv, W, h->bf16, false), plan(rt, W, qd, h->bf16, true),
+                         plan(rt, h->Ngu, W, h->bf16, false),  plan(rt, W, h->F, h->bf16, true)};
   for (const GemmPlan& p : ps) r.ws = std::max(r.ws, round256(p.ws_floats * 4));
   return r;
+}
+StepScratch step_scratch(const Handle* h, int B) {
+  return scratch_of(h, B, attn_split(h, B), plan_gemm);
+}
+// What fv_decode_step_noalloc asks for: the step's scratch, and at least the
+// tile kernels' plan of it with 512 attention workgroups, so that the steps
+// it refuses do not depend on which kernels a row count takes.
+size_t noalloc_bytes(const Handle* h, int B) {
+  return std::max(step_scratch(h, B).total(),
+                  scratch_of(h, B, attn_split_for(h, B, 512), plan_tiles).total());
 }
 
 // Points the handle's split partials and split-K workspace at caller-given
@@ -714,7 +737,9 @@ fv_status fv_create(const fv_weights* w, const fv_cfg* cfg, fv_handle* out) {
     lookup_static_scratch(H.device);
     if (H.bf16) {
       FV_HIP(gemm_prepare());
-      FV_HIP(attention_prepare());
+      FV_HIP(attention_prepare<bf16_t>());
+    } else {
+      FV_HIP(attention_prepare<float>());
     }
     FV_HIP(hipStreamCreateWithFlags(&H.cap_stream, hipStreamNonBlocking));
 
@@ -729,10 +754,10 @@ fv_status fv_create(const fv_weights* w, const fv_cfg* cfg, fv_handle* out) {
       std::vector<float> v;
       v.reserve((size_t)W * W);
       for (int c = 0; c < W; ++c) append_out_major(v, w->w_t1, W, W, c);
-      H.w_t1 = upload_T(h, v);
+      H.w_t1 = upload_T(h, v, W);
       v.clear();
       for (int c = 0; c < W; ++c) append_out_major(v, w->w_t2, W, W, c);
-      H.w_t2 = upload_T(h, v);
+      H.w_t2 = upload_T(h, v, W);
     }
     {
       std::vector<float> v, bias;
@@ -744,7 +769,7 @@ fv_status fv_create(const fv_weights* w, const fv_cfg* cfg, fv_handle* out) {
           bias.push_back(w->b_mod[n][c]);
         }
       }
-      H.w_mod = upload_T(h, v);
+      H.w_mod = upload_T(h, v, W);
       H.b_mod = upload_f32(h, bias.data(), bias.size(), true);
     }
     const int qd = H.Hq * dh, kd = H.Hkv * dh;
@@ -763,10 +788,10 @@ fv_status fv_create(const fv_weights* w, const fv_cfg* cfg, fv_handle* out) {
       for (int hq = 0; hq < H.Hq; ++hq) rot_head(w->wq[l], qd, hq);
       for (int g = 0; g < H.Hkv; ++g) rot_head(w->wk[l], kd, g);
       for (int c = 0; c < kd; ++c) append_out_major(v, w->wv[l], W, kd, c);
-      H.wqkv.push_back(upload_T(h, v));
+      H.wqkv.push_back(upload_T(h, v, W));
       v.clear();
       for (int c = 0; c < W; ++c) append_out_major(v, w->wo[l], qd, W, c);
-      H.wo.push_back(upload_T(h, v));
+      H.wo.push_back(upload_T(h, v, qd));
       v.clear();
       if (cfg->mlp_gated) {
         // gate/up partners packed into columns 64p + i and 64p + 32 + i, f = 32p + i
@@ -778,10 +803,10 @@ fv_status fv_create(const fv_weights* w, const fv_cfg* cfg, fv_handle* out) {
       } else {
         for (int c = 0; c < F; ++c) append_out_major(v, w->wu[l], W, F, c);
       }
-      H.wgu.push_back(upload_T(h, v));
+      H.wgu.push_back(upload_T(h, v, W));
       v.clear();
       for (int c = 0; c < W; ++c) append_out_major(v, w->wd[l], F, W, c);
-      H.wd.push_back(upload_T(h, v));
+      H.wd.push_back(upload_T(h, v, F));
     }
 
     // ---- rotary tables, built in fp64 and rounded to fp32
@@ -822,10 +847,11 @@ fv_status fv_create(const fv_weights* w, const fv_cfg* cfg, fv_handle* out) {
     H.cond = dalloc(h, rowsK * W * H.esz);
     H.mod = static_cast<float*>(dalloc(h, rowsK * H.Nmod * 4));
     H.hres = static_cast<float*>(dalloc(h, rowsT * W * 4));
-    H.u = dalloc(h, rowsT * W * H.esz);
+    const size_t rows16 = (rowsT + 15) / 16 * 16;  // whole tiles for the tiled layout
+    H.u = dalloc(h, rows16 * W * H.esz);
     H.q = dalloc(h, rowsT * qd * H.esz);
-    H.o = dalloc(h, rowsT * qd * H.esz);
-    H.m = dalloc(h, rowsT * F * H.esz);
+    H.o = dalloc(h, rows16 * qd * H.esz);
+    H.m = dalloc(h, rows16 * F * H.esz);
     H.v = static_cast<float*>(dalloc(h, rowsT * H.A * 4));
     size_t part_rows = 0;
     for (int B = 1; B <= H.Bmax; ++B) {
@@ -1015,9 +1041,10 @@ fv_status fv_decode_step_noalloc(fv_handle h, float* buffer, const float* t, flo
     const float* tt = schedule_or(h, t, B);
     const float* mod = t ? nullptr : h->mod_cache;
     const StepScratch need = step_scratch(h, B);
-    if (need.total() > kStaticScratchBytes)
+    const size_t asked = noalloc_bytes(h, B);
+    if (asked > kStaticScratchBytes)
       fail(FV_ERR_INVALID_ARG, "a step at batch " + std::to_string(B) + " needs " +
-                                   std::to_string(need.total()) +
+                                   std::to_string(asked) +
                                    " bytes of scratch; the static scratch holds " +
                                    std::to_string(kStaticScratchBytes) +
                                    " (use fv_decode_step)");
@@ -1285,7 +1312,7 @@ fv_status fv_query(fv_handle h, int32_t what, int32_t batch, int64_t* value) {
         break;
       case FV_QUERY_NOALLOC_SCRATCH_BYTES:
         if (batch < 1 || batch > h->Bmax) fail(FV_ERR_INVALID_ARG, "batch outside 1..max_batch");
-        *value = (int64_t)step_scratch(h, batch).total();
+        *value = (int64_t)noalloc_bytes(h, batch);
         break;
       default:
         fail(FV_ERR_INVALID_ARG, "unknown query");
