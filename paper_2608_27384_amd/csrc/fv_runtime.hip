@@ -176,7 +176,29 @@ int attn_split_for(const Handle* h, int B, int blocks) {
   const int s = (blocks + base - 1) / base;
   return s < 1 ? 1 : (s > 8 ? 8 : s);
 }
-int attn_split(const Handle* h, int B) { return attn_split_for(h, B, 512); }
+// The wide-head bf16 kernel (dh = 256) holds 128 KB of LDS, one workgroup per
+// CU, so splits that spill into another round of 256 workgroups cost more
+// than they save, and so does the combine they need where one round holds
+// all row tiles.  The estimate, in us: a round takes 8 of fixed costs and 1.1
+// per 32-key tile, the combine 3 and its partials at 4 MB per us (8 streams
+// of 500 tokens: 2 splits 66 + 20 per layer, none 53; 32 streams of 50: 4
+// splits 38 + 10, 2 splits 33).
+int attn_split(const Handle* h, int B) {
+  if (!h->bf16 || h->dh != 256 || few_rows(B * h->T)) return attn_split_for(h, B, 512);
+  const double base = (double)attention_row_tiles<bf16_t>(h->T, h->Hq, h->Hkv) * B * h->Hkv;
+  const double tiles = (h->Pmax + h->T + 31) / 32, part_mb = (double)B * h->T * h->Hq * 512e-6;
+  int best = 1;
+  double least = 0;
+  for (int s = 1; s <= 8; ++s) {
+    const double t = std::ceil(base * s / 256) * (8 + 1.1 * tiles / s) +
+                     (s > 1 ? 3 + s * part_mb / 4 : 0);
+    if (s == 1 || t < least) {
+      best = s;
+      least = t;
+    }
+  }
+  return best;
+}
 
 // ------------------------------------------------------------------ forward
 // Output projection / down projection with the gated residual, fused with
