@@ -130,6 +130,14 @@ __device__ __forceinline__ float wave_sum(float x) {
   return x;
 }
 
+// Sum over the lanes l, l ^ 16, l ^ 32, l ^ 48 (the lane swaps of wave_sum).
+__device__ __forceinline__ float sum_xor16_32(float x) {
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  const float y = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(y), __float_as_uint(y), false, false);
+  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
+
 // Pulls part of [p, p + bytes) into the chip's memory-side cache ahead of
 // the kernel that reads it next (the weights of the next GEMM, which would
 // otherwise come cold from HBM): thread t of the grid (NT threads per
@@ -290,7 +298,8 @@ void launch_time_embed(const float* t, T* e, int rows, int width, hipStream_t s,
 // sharing flag described above, or nullptr.  tiled (here and below): u goes
 // out in the tiled layout.
 template <typename T>
-void launch_embed_adarms(const float* x, const float* w_in, const float* b_in, float* h,
+void launch_embed_adarms(const float* x, const float* w_in, const float* w_in_t, const float* b_in,
+                         float* h,
                          const float* mod, int mod_ld, int chunk_len, float eps, T* u, int rows,
                          int A, int W, hipStream_t s, float* xs = nullptr,
                          const int* period = nullptr, bool tiled = false);
@@ -308,8 +317,8 @@ template <typename T>
 void launch_adarms(const float* h, const float* mod, int mod_ld, int scale_off, int chunk_len,
                    float eps, T* u, int rows, int W, hipStream_t s, const int* period = nullptr);
 void launch_final(const float* h, const float* mod, int mod_ld, int scale_off, int chunk_len,
-                  float eps, const float* w_out, const float* b_out, float* v, int rows, int W,
-                  int A, hipStream_t s, const int* period = nullptr);
+                  float eps, const float* w_out, const float* w_out_t, const float* b_out, float* v,
+                  int rows, int W, int A, hipStream_t s, const int* period = nullptr);
 // Destination of the Euler update fused into the velocity head (Algorithm 1:
 // x_k <- x_k - dt_k v_k, emit slot 0, shift, refill slot K-1): the caller's
 // buffer, the copy xs of it taken by the embedding at the start of the step,
@@ -329,8 +338,8 @@ bool head_fusable(int rows, int W, int A);
 // The velocity head with the Euler update, emission, shift and refill of
 // launch_euler_shift fused in (same rounding, same noise); v is not stored.
 void launch_final_euler(const float* h, const float* mod, int mod_ld, int scale_off, int chunk_len,
-                        float eps, const float* w_out, const float* b_out, int rows, int W, int A,
-                        const EulerDest& eu, hipStream_t s, const int* period = nullptr);
+                        float eps, const float* w_out, const float* w_out_t, const float* b_out,
+                        int rows, int W, int A, const EulerDest& eu, hipStream_t s, const int* period = nullptr);
 void launch_euler_shift(float* buffer, const float* t, const float* v, float* out,
                         const uint64_t* noise_state, uint32_t* ticket, int* n_valid, int B, int K,
                         int CA, hipStream_t s);
@@ -423,6 +432,8 @@ struct Handle {
   void* w_mod = nullptr;  float* b_mod = nullptr;  // T [Nmod][W], fp32 [Nmod]
   std::vector<void*> wqkv, wo, wgu, wd;            // T, out-major
   float* w_out = nullptr; float* b_out = nullptr;  // fp32 [W][A], [A]
+  // w_in and w_out transposed, in the tiled layout, zero past A (A <= 32, else nullptr)
+  float* w_in_t = nullptr; float* w_out_t = nullptr;  // fp32 [W][32], [32][W]
 
   // prefix arena and lengths
   void* karena = nullptr;   // [L][Bmax][Hkv][S][dh]

@@ -46,9 +46,11 @@ __global__ void time_embed_kernel(const float* __restrict__ t, T* __restrict__ e
 // of every row, reads w_in once for all rows in batches of independent
 // loads and keeps the x rows in LDS.
 constexpr int kEmbRows = 8;
-// Row count from which the embedding and the velocity head switch to their
-// weights-in-registers variants.
-constexpr int kManyRows = 4096;
+// Row count from which the embedding and the velocity head take the matrix
+// units, 16 rows per workgroup: 1600 rows 16.6 -> 12.7 and 18.7 -> 15.2 us,
+// 4000 rows 27 -> 14 and 40 -> 21; at 500 rows the small variants' 2 and 4
+// rows per workgroup spread wider (a batch-1 step is 14 us slower here).
+constexpr int kManyRows = 1024;
 
 __device__ __forceinline__ float block_sum_256(float v, float* red) {
   v = wave_sum(v);
@@ -221,91 +223,106 @@ __global__ __launch_bounds__(256) void embed_adarms_small_kernel(
   }
 }
 
-// Many rows (W <= 1024, A <= 32): thread t keeps its four columns of w_in in
-// registers and the block runs batches of kEmbRows rows through them, so
-// w_in is read once per block instead of once per batch.  The kernel holds
-// more than 256 registers per lane, so one workgroup fits a CU, and the grid
-// is sized to one round of them (launch_embed_adarms).  The next batch's x is requested at the
-// start of a batch and its modulation rows right after its arithmetic, so
-// their latency hides behind the arithmetic and the row-sum barrier.  Two barriers per batch: the one after the row sums
-// also keeps the next batch's x out of sx until every wave has read it, and
-// the one after sx is written keeps the next row sums out of sred until the
-// current ones are read.
+// Many rows (W <= 1024, A <= 32): the same product on the fp32 matrix units,
+// 16 rows per tile.  Wave w of eight holds the weights of columns [w W/8,
+// (w + 1) W/8) as MFMA operands in registers for all its tiles; the product
+// is formed transposed, so a lane gets four consecutive columns of row
+// l % 16, and the tile's rows of h and u go out as 64- and 32-byte runs.
+// Everything a tile reads is requested before its products (the next tile's
+// x during them), because one workgroup fits a CU: with the modulation read
+// where it is used a single tile took 17 us.  Bound by the 6 bytes per
+// element that h and u take: 32000 rows 120 -> 81 us (a VALU product,
+// eight rows at a time, before).  w_t: w_in in the tiled layout, [W][32],
+// zero past A.
 template <typename T>
-__global__ __launch_bounds__(256) void embed_adarms_rows_kernel(
-    const float* __restrict__ x, const float* __restrict__ w_in, const float* __restrict__ b_in,
+__global__ __launch_bounds__(512) void embed_adarms_mma_kernel(
+    const float* __restrict__ x, const float* __restrict__ w_t, const float* __restrict__ b_in,
     float* __restrict__ h, const float* __restrict__ mod, int mod_ld, int chunk_len, float eps,
-    T* __restrict__ u, int rows, int A, int W, int rows_per_block, const int* __restrict__ period) {
-  constexpr int R = kEmbRows;
-  __shared__ __attribute__((aligned(16))) float sx[32][R];
-  __shared__ float sred[R][4];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int c = 4 * tid;
-  const bool ok = c < W;
-  const int cc = min(c, W - 4);
-  const f32x4 zero4 = f32x4{0.f, 0.f, 0.f, 0.f};
-  f32x4 wv[32];
-#pragma unroll
-  for (int a = 0; a < 32; ++a)
-    wv[a] = ok && a < A ? *reinterpret_cast<const f32x4*>(w_in + (size_t)a * W + c) : zero4;
-  const f32x4 bias = ok ? *reinterpret_cast<const f32x4*>(b_in + c) : zero4;
+    T* __restrict__ u, int rows, int A, int W, float* __restrict__ xs,
+    const int* __restrict__ period) {
+  constexpr int NT = 8, NW = 8;  // 16-column tiles per wave at W = 1024; waves
+  __shared__ float sred[2][NW][16];
+  const int lane = threadIdx.x & 63, q = lane >> 4, l16 = lane & 15;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int nt = W / 128, c0 = wave * (W / NW);
   const int per = film_period(period);
-  const int rbeg = blockIdx.x * rows_per_block;
-  const int rend = min(rows, rbeg + rows_per_block);
-  // x of a batch: thread (r, a) = (tid / 32, tid % 32) holds entry a of row
-  // r (entries a >= A are zero, and so are their weights)
-  const int xr_r = tid >> 5, xr_a = tid & 31;
-  auto load_x = [&](int row0) __attribute__((always_inline)) {
-    return row0 + xr_r < rend && xr_a < A ? x[(size_t)(row0 + xr_r) * A + xr_a] : 0.f;
-  };
-  float xr = load_x(rbeg);
-  for (int row0 = rbeg; row0 < rend; row0 += R) {
-    sx[xr_a][xr_r] = xr;
-    xr = load_x(row0 + R);
-    __syncthreads();
-    f32x4 acc[R];
+  const bool vec = (A & 3) == 0;
+  // x entries k >= A read as zero
+  auto load_x = [&](int tile, u32x4 (&xv)[2]) __attribute__((always_inline)) {
+    const float* xrow = x + (size_t)min(16 * tile + l16, rows - 1) * A;
 #pragma unroll
-    for (int r = 0; r < R; ++r) acc[r] = bias;
+    for (int b = 0; b < 2; ++b) {
+      const int k = 16 * b + 4 * q;
+      if (vec) {
+        xv[b] = *reinterpret_cast<const u32x4*>(xrow + min(k, A - 4));
+      } else {
 #pragma unroll
-    for (int a = 0; a < 32; ++a) {
-      const f32x4 x0 = *reinterpret_cast<const f32x4*>(&sx[a][0]);
-      const f32x4 x1 = *reinterpret_cast<const f32x4*>(&sx[a][4]);
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        acc[r] += x0[r] * wv[a];
-        acc[4 + r] += x1[r] * wv[a];
+        for (int e = 0; e < 4; ++e) xv[b][e] = __float_as_uint(xrow[min(k + e, A - 1)]);
       }
-      if ((a & 7) == 7) __builtin_amdgcn_sched_barrier(0);  // bounds the LDS reads in flight
-    }
-    // the modulation rows, in flight during the stores and the row-sum barrier
-    f32x4 sv[R], bv[R];
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const int row = min(row0 + r, rend - 1);
-      const float* sc = mod + (size_t)film_row(row / chunk_len, per) * mod_ld;
-      sv[r] = *reinterpret_cast<const f32x4*>(sc + cc);
-      bv[r] = *reinterpret_cast<const f32x4*>(sc + W + cc);
+      for (int e = 0; e < 4; ++e) xv[b][e] = k + e < A ? xv[b][e] : 0u;
+    }
+  };
+  const int tiles = (rows + 15) / 16;
+  u32x4 xv[2], wv[NT][2];
+  load_x(min((int)blockIdx.x, tiles - 1), xv);
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+      wv[t][b] = *reinterpret_cast<const u32x4*>(
+          w_t + tile_off<float>(c0 + 16 * min(t, nt - 1) + l16, 16 * b + 4 * q, 32));
+  int it = 0;
+  for (int tile = blockIdx.x; tile < tiles; tile += gridDim.x, it ^= 1) {
+    const int row = 16 * tile + l16, rc = min(row, rows - 1);
+    const float* sc = mod + (size_t)film_row(rc / chunk_len, per) * mod_ld + c0 + 4 * q;
+    f32x4 acc[NT], sv[NT], bv[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      const int c = 16 * min(t, nt - 1);
+      acc[t] = *reinterpret_cast<const f32x4*>(b_in + c0 + c + 4 * q);
+      sv[t] = *reinterpret_cast<const f32x4*>(sc + c);
+      bv[t] = *reinterpret_cast<const f32x4*>(sc + W + c);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if (xs && wave == 0 && row < rows) {
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (16 * b + 4 * q + e < A)
+            xs[(size_t)row * A + 16 * b + 4 * q + e] = __uint_as_float(xv[b][e]);
     }
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const float ss = acc[r][0] * acc[r][0] + acc[r][1] * acc[r][1] + acc[r][2] * acc[r][2] +
-                       acc[r][3] * acc[r][3];
-      if (ok && row0 + r < rend) *reinterpret_cast<f32x4*>(h + (size_t)(row0 + r) * W + c) = acc[r];
-      const float v = wave_sum(ok ? ss : 0.f);
-      if (lane == 0) sred[r][wave] = v;
-    }
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int b = 0; b < 2; ++b) acc[t] = mma64(wv[t][b], xv[b], acc[t], float());
+    if (tile + (int)gridDim.x < tiles) load_x(tile + gridDim.x, xv);
+    float ss = 0.f;
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+      if (t < nt) {
+        ss += acc[t][0] * acc[t][0] + acc[t][1] * acc[t][1] + acc[t][2] * acc[t][2] +
+              acc[t][3] * acc[t][3];
+        if (row < rows)
+          *reinterpret_cast<f32x4*>(h + (size_t)row * W + c0 + 16 * t + 4 * q) = acc[t];
+      }
+    ss = sum_xor16_32(ss);
+    if (lane < 16) sred[it][wave][lane] = ss;
+    // one barrier per tile: the next tile writes the other half of sred
     __syncthreads();
+    float tot = 0.f;
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const int row = row0 + r;
-      if (row >= rend || !ok) break;
-      const float tot = sred[r][0] + sred[r][1] + sred[r][2] + sred[r][3];
-      const float rinv = 1.0f / sqrtf(tot / (float)W + eps);
-      store4<T>(u + (size_t)row * W + c, acc[r][0] * rinv * (1.0f + sv[r][0]) + bv[r][0],
-                acc[r][1] * rinv * (1.0f + sv[r][1]) + bv[r][1],
-                acc[r][2] * rinv * (1.0f + sv[r][2]) + bv[r][2],
-                acc[r][3] * rinv * (1.0f + sv[r][3]) + bv[r][3]);
-    }
+    for (int w = 0; w < NW; ++w) tot += sred[it][w][l16];
+    const float rinv = 1.0f / sqrtf(tot / (float)W + eps);
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+      if (t < nt && row < rows)
+        store4<T>(u + (size_t)row * W + c0 + 16 * t + 4 * q,
+                  acc[t][0] * rinv * (1.0f + sv[t][0]) + bv[t][0],
+                  acc[t][1] * rinv * (1.0f + sv[t][1]) + bv[t][1],
+                  acc[t][2] * rinv * (1.0f + sv[t][2]) + bv[t][2],
+                  acc[t][3] * rinv * (1.0f + sv[t][3]) + bv[t][3]);
   }
 }
 
@@ -719,98 +736,123 @@ __global__ __launch_bounds__(256) void final_small_kernel(const float* __restric
   if constexpr (EU) euler_finish(eu, rows / (eu.K * chunk_len), step);
 }
 
-// Many rows (W <= 1024, A <= 32, A % 4 == 0): 512 threads; thread (part, q)
-// keeps rows 16 part .. 16 part + 15 of w_out at outputs 4q .. 4q + 3 in
-// registers and the block runs batches of 8 rows (one per wave) through
-// them: w_out is read once per block, and every normalised value read from
-// LDS feeds four outputs.  The 8 parts of a wave are added across lanes
-// (lane bits 5, 4, 3) and the 8 waves in a fixed order.  One workgroup per
-// CU and a grid of one round (launch_final); each wave requests its next row
-// (h, scale, shift) as soon as the current one is in LDS, so the load latency
-// hides behind the head's arithmetic.  Two barriers per batch: the one after
-// the partial sums also keeps the next rows out of su until every wave has
-// read it, and the one after su is written keeps the next partial sums out
-// of sp until the current ones are added.
-constexpr int kFinalRowsBig = 8;
-__global__ __launch_bounds__(512) void final_rows_kernel(const float* __restrict__ h,
-                                                         const float* __restrict__ mod, int mod_ld,
-                                                         int scale_off, int chunk_len, float eps,
-                                                         const float* __restrict__ w_out,
-                                                         const float* __restrict__ b_out,
-                                                         float* __restrict__ v, int rows, int W,
-                                                         int A, int rows_per_block,
-                                                         const int* __restrict__ period) {
-  constexpr int R = kFinalRowsBig, KS = 16, NPL = 1024 / 64;
-  __shared__ __attribute__((aligned(16))) float su[R][1024];  // zero past W
-  __shared__ f32x4 sp[8][R][8];                                 // [wave][row][quad]
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, tid = threadIdx.x;
-  const int q = tid & 7, part = tid >> 3;
-  const int qa = min(4 * q, A - 4);
-  const int k0 = KS * part;
-  f32x4 wr[KS];
-#pragma unroll
-  for (int j = 0; j < KS; ++j)
-    wr[j] = k0 + j < W && 4 * q < A ? *reinterpret_cast<const f32x4*>(w_out + (size_t)(k0 + j) * A + qa)
-                                    : f32x4{0.f, 0.f, 0.f, 0.f};
-  const f32x4 bo = *reinterpret_cast<const f32x4*>(b_out + qa);
+// Many rows (W <= 1024, W % 128 == 0, A <= 32, A % 4 == 0): the same head on
+// the fp32 matrix units, 16 rows per tile.  Wave w of eight takes the eighth
+// [w W/8, (w + 1) W/8) of the width: it loads those pieces of the tile's rows
+// and of their modulation as MFMA operands, the row sums meet in LDS, and
+// the normalised pieces multiply the wave's part of w_out, which stays in
+// registers for all tiles; the eight partial products are added in wave
+// order.  The next tile's rows are requested as soon as this tile's are
+// normalised.  With EU the threads that hold the velocities apply the Euler
+// update as final_small_kernel<true> does.  Bound by reading h: 32000 rows
+// 92 -> 51 us (VALU products before), and the separate 32 us queue
+// update is gone.  w_t: w_out in the tiled layout, [32][W], zero past A.
+template <bool EU>
+__global__ __launch_bounds__(512) void final_mma_kernel(const float* __restrict__ h,
+                                                        const float* __restrict__ mod, int mod_ld,
+                                                        int scale_off, int chunk_len, float eps,
+                                                        const float* __restrict__ w_t,
+                                                        const float* __restrict__ b_out,
+                                                        float* __restrict__ v, int rows, int W,
+                                                        int A, EulerDest eu,
+                                                        const int* __restrict__ period) {
+  constexpr int NB = 8;  // 16-wide k blocks per wave at W = 1024
+  __shared__ float sred[8][16];
+  __shared__ f32x4 sp[8][2][64];
+  const int tid = threadIdx.x, lane = tid & 63, q = lane >> 4, l16 = lane & 15;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int nb = W / 128, k0 = wave * (W / 8);
   const int per = film_period(period);
-  const int rbeg = blockIdx.x * rows_per_block;
-  const int rend = min(rows, rbeg + rows_per_block);
-  float hv[NPL], sv[NPL], bv[NPL];
-  auto load_row = [&](int row0) __attribute__((always_inline)) {  // this wave's row of a batch
-    const int row = min(row0 + wave, rend - 1);
-    const float* hr = h + (size_t)row * W;
-    const float* sc = mod + (size_t)film_row(row / chunk_len, per) * mod_ld + scale_off;
+  u32x4 wr[2][NB];
 #pragma unroll
-    for (int i = 0; i < NPL; ++i) {
-      const int cc = min(lane + 64 * i, W - 1);
-      hv[i] = hr[cc];
-      sv[i] = sc[cc];
-      bv[i] = sc[W + cc];
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+      wr[t][j] = *reinterpret_cast<const u32x4*>(
+          w_t + tile_off<float>(16 * t + l16, k0 + 16 * min(j, nb - 1) + 4 * q, W));
+  // the output quad of a thread of the first two waves
+  const int oa = 16 * (wave & 1) + 4 * q, oac = min(oa, A - 4);
+  const f32x4 bo = *reinterpret_cast<const f32x4*>(b_out + oac);
+  uint64_t seed = 0, step = 0;
+  if constexpr (EU) {
+    seed = eu.noise_state[0];
+    step = eu.noise_state[1];
+  }
+  f32x4 hv[NB], sv[NB], bv[NB];
+  auto load_tile = [&](int tile) __attribute__((always_inline)) {
+    const int row = min(16 * tile + l16, rows - 1);
+    const float* hr = h + (size_t)row * W + k0 + 4 * q;
+    const float* sc =
+        mod + (size_t)film_row(row / chunk_len, per) * mod_ld + scale_off + k0 + 4 * q;
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      const int c = 16 * min(j, nb - 1);
+      hv[j] = *reinterpret_cast<const f32x4*>(hr + c);
+      sv[j] = *reinterpret_cast<const f32x4*>(sc + c);
+      bv[j] = *reinterpret_cast<const f32x4*>(sc + W + c);
     }
   };
-  if (rbeg < rend) load_row(rbeg);
-  for (int row0 = rbeg; row0 < rend; row0 += R) {
-    {
-      float ss = 0.f;
+  const int tiles = (rows + 15) / 16;
+  if ((int)blockIdx.x < tiles) load_tile(blockIdx.x);
+  for (int tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+    const int row = 16 * tile + l16;
+    float ss = 0.f;
 #pragma unroll
-      for (int i = 0; i < NPL; ++i) ss += lane + 64 * i < W ? hv[i] * hv[i] : 0.f;
-      ss = wave_sum(ss);
-      const float rinv = 1.0f / sqrtf(ss / (float)W + eps);
-#pragma unroll
-      for (int i = 0; i < NPL; ++i) {
-        const int cc = lane + 64 * i;
-        su[wave][cc] = cc < W ? hv[i] * rinv * (1.0f + sv[i]) + bv[i] : 0.f;
-      }
-    }
-    if (row0 + R < rend) load_row(row0 + R);
+    for (int j = 0; j < NB; ++j)
+      if (j < nb)
+        ss += hv[j][0] * hv[j][0] + hv[j][1] * hv[j][1] + hv[j][2] * hv[j][2] +
+              hv[j][3] * hv[j][3];
+    ss = sum_xor16_32(ss);
+    if (lane < 16) sred[wave][lane] = ss;
     __syncthreads();
+    float tot = 0.f;
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    for (int w = 0; w < 8; ++w) tot += sred[w][l16];
+    const float rinv = 1.0f / sqrtf(tot / (float)W + eps);
+    f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
-      for (int j = 0; j < KS; j += 4) {
-        const f32x4 x4 = *reinterpret_cast<const f32x4*>(&su[r][k0 + j]);
-        acc += x4[0] * wr[j];
-        acc += x4[1] * wr[j + 1];
-        acc += x4[2] * wr[j + 2];
-        acc += x4[3] * wr[j + 3];
+    for (int j = 0; j < NB; ++j)
+      if (j < nb) {
+        u32x4 un;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          un[e] = __float_as_uint(hv[j][e] * rinv * (1.0f + sv[j][e]) + bv[j][e]);
+#pragma unroll
+        for (int t = 0; t < 2; ++t) acc[t] = mma64(wr[t][j], un, acc[t], float());
       }
-#pragma unroll
-      for (int e = 0; e < 4; ++e) acc[e] = sum_lane_bits_543(acc[e]);
-      if (lane < 8) sp[wave][r][lane] = acc;
+    if (tile + (int)gridDim.x < tiles) load_tile(tile + gridDim.x);
+    sp[wave][0][lane] = acc[0];
+    sp[wave][1][lane] = acc[1];
+    int b = 0, k = 0, nvalid = 0;
+    float tk = 0.f, tp = 0.f;
+    f32x4 x4 = {0.f, 0.f, 0.f, 0.f};
+    if (EU && wave < 2) {  // the output threads' slots, requested ahead of the sums
+      const int rc = min(row, rows - 1), T = eu.K * chunk_len;
+      b = rc / T;
+      k = (rc - b * T) / chunk_len;
+      tk = eu.t[(size_t)b * eu.K + k];
+      tp = eu.t[(size_t)b * eu.K + max(k - 1, 0)];
+      x4 = *reinterpret_cast<const f32x4*>(eu.xs + (size_t)rc * A + oac);
+      nvalid = eu.n_valid[b];
     }
+    // two barriers per tile: the first also keeps sp until it has been read,
+    // the second sred
     __syncthreads();
-    if (tid < R * 8) {
-      const int r = tid >> 3;
-      if (row0 + r < rend && 4 * q < A) {
-        f32x4 vv = bo;
+    if (wave < 2 && row < rows && oa < A) {
+      f32x4 vv = sp[0][wave][lane];
 #pragma unroll
-        for (int w = 0; w < 8; ++w) vv += sp[w][r][q];
-        *reinterpret_cast<f32x4*>(v + (size_t)(row0 + r) * A + 4 * q) = vv;
+      for (int w = 1; w < 8; ++w) vv += sp[w][wave][lane];
+      vv += bo;
+      const size_t base = (size_t)row * A + oa;
+      if constexpr (!EU) {
+        *reinterpret_cast<f32x4*>(v + base) = vv;
+      } else {
+        euler_group(eu, vv, x4, tk - (k > 0 ? tp : 0.f), b, k, nvalid >= eu.K,
+                    row % chunk_len * (A / 4) + oa / 4, base, chunk_len * A, seed, step);
       }
     }
   }
+  if constexpr (EU) euler_finish(eu, rows / (eu.K * chunk_len), step);
 }
 
 // ------------------------------------------- Euler + emit + shift + refill
@@ -998,19 +1040,19 @@ void launch_time_embed(const float* t, T* e, int rows, int width, hipStream_t s,
 }
 
 bool head_fusable(int rows, int W, int A) {
-  return rows < kManyRows && W <= 1024 && W % 4 == 0 && A <= 32 && A % 4 == 0;
+  return W <= 1024 && W % 128 == 0 && A <= 32 && A % 4 == 0;
 }
 
 template <typename T>
-void launch_embed_adarms(const float* x, const float* w_in, const float* b_in, float* h,
+void launch_embed_adarms(const float* x, const float* w_in, const float* w_in_t, const float* b_in,
+                         float* h,
                          const float* mod, int mod_ld, int chunk_len, float eps, T* u, int rows,
                          int A, int W, hipStream_t s, float* xs, const int* period,
                          bool tiled) {
   if (rows >= kManyRows && W <= 1024 && A <= 32) {
-    // one round of one workgroup per CU
-    const int rpb = kEmbRows * ((rows + kEmbRows * 256 - 1) / (kEmbRows * 256));
-    hipLaunchKernelGGL((embed_adarms_rows_kernel<T>), dim3((rows + rpb - 1) / rpb), dim3(256), 0, s,
-                       x, w_in, b_in, h, mod, mod_ld, chunk_len, eps, u, rows, A, W, rpb, period);
+    hipLaunchKernelGGL((embed_adarms_mma_kernel<T>), dim3(std::min(256, (rows + 15) / 16)), dim3(512),
+                       0, s, x, w_in_t, b_in, h, mod, mod_ld, chunk_len, eps, u, rows, A, W, xs,
+                       period);
     return;
   }
   if (W <= 1024 && W % 4 == 0 && A <= 32) {
@@ -1060,14 +1102,13 @@ void launch_adarms(const float* h, const float* mod, int mod_ld, int scale_off, 
 }
 
 void launch_final(const float* h, const float* mod, int mod_ld, int scale_off, int chunk_len,
-                  float eps, const float* w_out, const float* b_out, float* v, int rows, int W,
-                  int A, hipStream_t s, const int* period) {
+                  float eps, const float* w_out, const float* w_out_t, const float* b_out, float* v,
+                  int rows, int W, int A, hipStream_t s, const int* period) {
   const size_t lds = (size_t)(kFinalRows * W + 256 * kFinalRows) * sizeof(float);
-  if (rows >= kManyRows && W <= 1024 && W % 4 == 0 && A <= 32 && A % 4 == 0) {
-    // one round of one workgroup per CU
-    const int rpb = kFinalRowsBig * ((rows + kFinalRowsBig * 256 - 1) / (kFinalRowsBig * 256));
-    hipLaunchKernelGGL(final_rows_kernel, dim3((rows + rpb - 1) / rpb), dim3(512), 0, s, h, mod,
-                       mod_ld, scale_off, chunk_len, eps, w_out, b_out, v, rows, W, A, rpb, period);
+  if (rows >= kManyRows && head_fusable(rows, W, A)) {
+    hipLaunchKernelGGL(final_mma_kernel<false>, dim3(std::min(256, (rows + 15) / 16)), dim3(512), 0,
+                       s, h, mod, mod_ld, scale_off, chunk_len, eps, w_out_t, b_out, v, rows, W, A,
+                       EulerDest{}, period);
     return;
   }
   if (W <= 1024 && A <= 32 && A % 4 == 0) {
@@ -1081,8 +1122,15 @@ void launch_final(const float* h, const float* mod, int mod_ld, int scale_off, i
 }
 
 void launch_final_euler(const float* h, const float* mod, int mod_ld, int scale_off, int chunk_len,
-                        float eps, const float* w_out, const float* b_out, int rows, int W, int A,
-                        const EulerDest& eu, hipStream_t s, const int* period) {
+                        float eps, const float* w_out, const float* w_out_t, const float* b_out,
+                        int rows, int W, int A, const EulerDest& eu, hipStream_t s,
+                        const int* period) {
+  if (rows >= kManyRows) {
+    hipLaunchKernelGGL(final_mma_kernel<true>, dim3(std::min(256, (rows + 15) / 16)), dim3(512), 0, s,
+                       h, mod, mod_ld, scale_off, chunk_len, eps, w_out_t, b_out, nullptr, rows, W, A,
+                       eu, period);
+    return;
+  }
   hipLaunchKernelGGL(final_small_kernel<true>, dim3((rows + kFinalSmallRows - 1) / kFinalSmallRows),
                      dim3(256), 0, s, h, mod, mod_ld, scale_off, chunk_len, eps, w_out, b_out,
                      nullptr, rows, W, A, eu, period);
@@ -1130,10 +1178,10 @@ void launch_prefix_copy(const T* k, const T* v, int L, int B, int src_batch, int
 
 template void launch_time_embed<bf16_t>(const float*, bf16_t*, int, int, hipStream_t, int*, int);
 template void launch_time_embed<float>(const float*, float*, int, int, hipStream_t, int*, int);
-template void launch_embed_adarms<bf16_t>(const float*, const float*, const float*, float*,
+template void launch_embed_adarms<bf16_t>(const float*, const float*, const float*, const float*, float*,
                                           const float*, int, int, float, bf16_t*, int, int, int,
                                           hipStream_t, float*, const int*, bool);
-template void launch_embed_adarms<float>(const float*, const float*, const float*, float*,
+template void launch_embed_adarms<float>(const float*, const float*, const float*, const float*, float*,
                                          const float*, int, int, float, float*, int, int, int,
                                          hipStream_t, float*, const int*, bool);
 template void launch_resid_norm<bf16_t>(const void*, bool, int, float*, const float*, int, int,

@@ -291,7 +291,7 @@ bool enqueue_forward(Handle* h, const float* buffer, const float* t, int B, floa
     mod = h->mod;
   }
   h->film_per = mod_cached ? nullptr : per;  // the flag that goes with h->mod (debug stages)
-  launch_embed_adarms<T>(buffer, h->w_in, h->b_in, h->hres, mod, Nmod, h->C, h->cfg.rms_eps,
+  launch_embed_adarms<T>(buffer, h->w_in, h->w_in_t, h->b_in, h->hres, mod, Nmod, h->C, h->cfg.rms_eps,
                          (T*)h->u, rowsT, h->A, W, s, fuse ? h->v : nullptr, per, few_rows(rowsT));
   const int n_split = attn_split(h, B);
   for (int l = 0; l < n_layers_run; ++l) {
@@ -326,12 +326,12 @@ bool enqueue_forward(Handle* h, const float* buffer, const float* t, int B, floa
     EulerDest d = *eu;
     d.xs = h->v;
     launch_final_euler(h->hres, mod, Nmod, 6 * h->L * W, h->C, h->cfg.rms_eps, h->w_out,
-                       h->b_out, rowsT, W, h->A, d, s, per);
+                       h->w_out_t, h->b_out, rowsT, W, h->A, d, s, per);
     return true;
   }
   if (v_out)
-    launch_final(h->hres, mod, Nmod, 6 * h->L * W, h->C, h->cfg.rms_eps, h->w_out, h->b_out,
-                 v_out, rowsT, W, h->A, s, per);
+    launch_final(h->hres, mod, Nmod, 6 * h->L * W, h->C, h->cfg.rms_eps, h->w_out,
+                 h->w_out_t, h->b_out, v_out, rowsT, W, h->A, s, per);
   return false;
 }
 
@@ -772,6 +772,22 @@ fv_status fv_create(const fv_weights* w, const fv_cfg* cfg, fv_handle* out) {
     H.b_t2 = upload_f32(h, w->b_t2, W, true);
     H.w_out = upload_f32(h, w->w_out, (size_t)W * H.A, true);
     H.b_out = upload_f32(h, w->b_out, H.A, true);
+    if (H.A <= 32) {
+      auto rounded = [&](float x) {
+        if (!H.bf16) return x;
+        const uint32_t u = (uint32_t)host_bf16(x) << 16;
+        std::memcpy(&x, &u, 4);
+        return x;
+      };
+      std::vector<float> in_t((size_t)W * 32), out_t((size_t)32 * W);
+      for (int c = 0; c < W; ++c)
+        for (int a = 0; a < H.A; ++a) {
+          in_t[(size_t)c * 32 + a] = w->w_in[(size_t)a * W + c];
+          out_t[(size_t)a * W + c] = w->w_out[(size_t)c * H.A + a];
+        }
+      H.w_in_t = static_cast<float*>(upload_tiled<float>(h, in_t, 32, rounded));
+      H.w_out_t = static_cast<float*>(upload_tiled<float>(h, out_t, W, rounded));
+    }
     {
       std::vector<float> v;
       v.reserve((size_t)W * W);
