@@ -1115,21 +1115,18 @@ GemmPlan plan_tiles(int M, int N, int K, bool bf16, bool reduce_fused) {
   if (N % 128 || M <= 0) return p;
   const int bk = bf16 ? 64 : 32, nk = K / bk;
   auto ntiles = [&](int t) { return ((M + kTileBM[t] - 1) / kTileBM[t]) * (N / kTileBN[t]); };
-  if (M >= 4096) {
-    // 256x256 tiles run one workgroup per CU, 128x128 tiles two.  A grid of
-    // two rounds of 256x256 tiles whose second round is mostly idle (under 72
-    // of 256 tiles) takes 128x128 tiles instead: measured per step, batch 16
-    // (QKV, 64 tiles in round two) 7.82 -> 7.67 ms, batch 36 (output and
-    // down projections, 28) 17.67 -> 17.00, batch 40 (60) 19.03 -> 18.73;
-    // slower at batch 44 (88) and 48 (120)
-    const long n256 = ntiles(T256x256big);
-    const bool big = n256 >= 200 && !(n256 > 256 && n256 <= 512 && n256 % 256 < 72);
-    if (!bf16)
-      p.tile = T256x128w8;
-    else if (N % 256 == 0 && big)
-      p.tile = T256x256big;
-    else
-      p.tile = N % 256 == 0 ? T128x128w8 : T256x128w8;
+  // 256x256 tiles run one workgroup per CU, 128x128 tiles two.  A grid of
+  // two rounds of 256x256 tiles whose second round is mostly idle (under 72
+  // of 256 tiles) takes 128x128 tiles instead: measured per step, batch 16
+  // (QKV, 64 tiles in round two) 7.82 -> 7.67 ms, batch 36 (output and
+  // down projections, 28) 17.67 -> 17.00, batch 40 (60) 19.03 -> 18.73;
+  // slower at batch 44 (88) and 48 (120).  Two full rounds are best on
+  // 256x256 tiles, also below 4096 rows (4000 rows, gate/up 83.6 -> 73.1 us).
+  const long n256 = ntiles(T256x256big);
+  if (bf16 && M >= 2048 && N % 256 == 0 && n256 >= 200 && !(n256 > 256 && n256 < 328)) {
+    p.tile = T256x256big;
+  } else if (M >= 4096) {
+    p.tile = bf16 && N % 256 == 0 ? T128x128w8 : T256x128w8;
   } else if (M > 256) {
     // (an output or down projection takes 128x128 tiles from 96 of them on:
     // with k split in two they beat 64x128 tiles, batch 3 2790 -> 2722 us)
