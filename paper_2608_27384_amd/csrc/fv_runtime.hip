@@ -182,14 +182,17 @@ int attn_split_for(const Handle* h, int B, int blocks) {
 // all row tiles.  The estimate, in us: a round takes 8 of fixed costs and 1.1
 // per 32-key tile, the combine 3 and its partials at 4 MB per us (8 streams
 // of 500 tokens: 2 splits 66 + 20 per layer, none 53; 32 streams of 50: 4
-// splits 38 + 10, 2 splits 33).
+// splits 38 + 10, 2 splits 33).  Never more splits than for 512 workgroups:
+// the partials' memory, and with it the steps that fit the static scratch,
+// is bounded by that count.
 int attn_split(const Handle* h, int B) {
-  if (!h->bf16 || h->dh != 256 || few_rows(B * h->T)) return attn_split_for(h, B, 512);
+  const int cap = attn_split_for(h, B, 512);
+  if (!h->bf16 || h->dh != 256 || few_rows(B * h->T)) return cap;
   const double base = (double)attention_row_tiles<bf16_t>(h->T, h->Hq, h->Hkv) * B * h->Hkv;
   const double tiles = (h->Pmax + h->T + 31) / 32, part_mb = (double)B * h->T * h->Hq * 512e-6;
   int best = 1;
   double least = 0;
-  for (int s = 1; s <= 8; ++s) {
+  for (int s = 1; s <= cap; ++s) {
     const double t = std::ceil(base * s / 256) * (8 + 1.1 * tiles / s) +
                      (s > 1 ? 3 + s * part_mb / 4 : 0);
     if (s == 1 || t < least) {
