@@ -40,7 +40,16 @@ namespace fv {
 namespace {
 
 constexpr float kSlack = 8.0f;  // lazy softmax reference slack (log2 units)
-constexpr float kHeadroom = 64.0f;  // fixed-reference headroom of the bf16 kernel (log2 units)
+constexpr float kHeadroom = 64.0f;  // fixed-reference headroom of the bf16 kernels (log2 units)
+// The 16-row kernels look at a lane's sum of 8 probabilities per tile instead
+// of the row's maximum (no maximum, no lane exchange on the common path): a
+// sum above 2^kHeadroom means some score is more than 61 above its row's
+// reference, and rows more than kRaise above theirs then take a new one.
+constexpr float kSumLimit = 18446744073709551616.0f;  // 2^kHeadroom
+constexpr float kRaise = kHeadroom - 4.0f;
+// Minus the reference of a row that has seen no key: a visible score then
+// gives an infinite probability (noticed), a masked one (-inf) still 0.
+constexpr float kNoRef = 3.402823466e38f;
 constexpr int kRG = 1;          // 16-row MFMA groups per wave
 constexpr int kRowsPerBlock = 4 * 16 * kRG;
 constexpr int kAttn16Waves = 8;  // bf16 kernel: 8 waves x 16 rows
@@ -351,11 +360,6 @@ __device__ __forceinline__ float max_xor16_32(float x) {
   const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(y), __float_as_uint(y), false, false);
   return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
 }
-// (a plain function: the load builtin written directly in a kernel template
-// body loses the template's host-side launch stub)
-__device__ __forceinline__ void lds_dma16_attn(const void* src, void* lds) {
-  __builtin_amdgcn_global_load_lds(src, lds, 16, 0, 0);
-}
 template <int N>
 __device__ __forceinline__ void wait_vmcnt_attn() {  // at most N vector memory ops outstanding
   __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (0x7 << 4) | (0xF << 8));
@@ -492,28 +496,29 @@ __global__ __launch_bounds__(64 * NWV) void attn16_kernel(AttnArgs a) {
     }
   };
 
-  // Softmax with a fixed per-row reference m_ref: probabilities are
-  // exp2(s - m_ref) and may exceed 1 by up to 2^kHeadroom, which fp32 sums
-  // and bf16 probabilities represent exactly as well as values below 1.  The
-  // inner loop touches the accumulators only through MFMAs; when a row's
-  // score would pass the headroom (always on the first tile, rarely later)
-  // the loop stops, the accumulators are rescaled once and the same tile is
-  // processed again against the raised reference.
+  // Softmax with a fixed per-row reference, the row's maximum over its first
+  // visible tile: probabilities are exp2(s - m) and may exceed 1 by up to
+  // 2^kHeadroom, which fp32 sums and bf16 probabilities represent exactly as
+  // well as values below 1.  The inner loop touches the accumulators only
+  // through MFMAs; when a row's scores pass the headroom (rare) the loop
+  // stops, the accumulators are rescaled once and the same tile is processed
+  // again against the raised reference.  A lane keeps its own share of the
+  // row sum; the four lanes of a row meet after the last tile.
   const int kt_clamp = max(kt_begin, kt_end - 1);
   load_tile(kts.tile(min(kt_begin, kt_clamp)));
   int kt = kt_begin;
-  bool staged = false;
+  bool redo = false;  // the tile runs again, against the raised references
+  float m_neg = kNoRef;  // minus the row's reference
   float m_pending = -INFINITY;
   while (kt < kt_end) {
     for (; kt < kt_end; ++kt) {
       const int key0 = kts.tile(kt) * KT;
-      if (!staged) {
+      if (!redo) {
         __syncthreads();  // previous tile fully consumed
         store_tile();
         __syncthreads();
         load_tile(kts.tile(min(kt + 1, kt_clamp)));  // overlaps the MFMA work below
       }
-      staged = false;
 
       // S^T per 16-key half: two chains each (even / odd k steps)
       f32x4 s[2][2] = {{f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}},
@@ -541,26 +546,40 @@ __global__ __launch_bounds__(64 * NWV) void attn16_kernel(AttnArgs a) {
           if (!(key < P || (key >= klo && key < khi))) sc[e] = -INFINITY;
         }
       }
-      float mt = sc[0];
-#pragma unroll
-      for (int e = 1; e < 8; ++e) mt = fmaxf(mt, sc[e]);
-      mt = max_xor16_32(mt) * sl2;
-      if (m_run == -INFINITY) m_run = mt;
-      if (__any(mt > m_run + kHeadroom)) {
-        m_pending = mt;
-        staged = true;
-        break;
-      }
-      const float m_use = m_run == -INFINITY ? 0.f : m_run;
-      float ls = 0.f;
+      // probabilities against the fixed reference (raw hardware exp2: one
+      // below 2^-126, flushed to 0, is negligible against the row's sum)
+      float ls;
       u16x8 pb;
+      auto probs = [&]() __attribute__((always_inline)) {
+        ls = 0.f;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const float p = __builtin_amdgcn_exp2f(fmaf(sc[e], sl2, -m_use));  // see attn16d_kernel
-        ls += p;
-        pb[e] = f32_to_bf16(p);
+        for (int e = 0; e < 8; ++e) {
+          const float p = __builtin_amdgcn_exp2f(fmaf(sc[e], sl2, m_neg));
+          ls += p;
+          pb[e] = f32_to_bf16(p);
+        }
+      };
+      probs();
+      // some lane's share of a row sum passed the headroom (inf while the row
+      // has no reference)
+      if (!redo && __any(!(ls <= kSumLimit))) {
+        float mt = sc[0];
+#pragma unroll
+        for (int e = 1; e < 8; ++e) mt = fmaxf(mt, sc[e]);
+        mt = max_xor16_32(mt) * sl2;
+        if (m_run == -INFINITY) {  // the row's first keys: nothing to rescale
+          m_run = mt;
+          m_neg = mt == -INFINITY ? kNoRef : -mt;
+        }
+        if (__any(mt > m_run + kRaise)) {
+          m_pending = mt;
+          redo = true;
+          break;
+        }
+        probs();
       }
-      l_run += sum_xor16_32(ls);
+      redo = false;
+      l_run += ls;
       const bf16x8 pf = __builtin_bit_cast(bf16x8, pb);
       // O^T (dh x queries) += V^T P^T: dh row 16 dt + l16, keys 4 lg + 0..3
       // and 16 + 4 lg + 0..3
@@ -574,18 +593,20 @@ __global__ __launch_bounds__(64 * NWV) void attn16_kernel(AttnArgs a) {
         acc[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, pf, acc[dt], 0, 0, 0);
       }
     }
-    if (staged) {
-      const float m_new = m_pending > m_run + kHeadroom ? m_pending : m_run;
+    if (redo) {
+      const float m_new = m_pending > m_run + kRaise ? m_pending : m_run;
       const float alpha = m_run == -INFINITY ? 0.f : exp2f(m_run - m_new);
       l_run *= alpha;
 #pragma unroll
       for (int dt = 0; dt < NDT; ++dt) acc[dt] *= alpha;
       m_run = m_new;
+      m_neg = m_run == -INFINITY ? kNoRef : -m_run;
     }
   }
 
   // Normalised output through LDS: lane (query l16, group lg) holds dh
   // 16 dt + 4 lg + 0..3; rows then go out whole, 16 bytes per lane.
+  l_run = sum_xor16_32(l_run);
   const size_t R = (size_t)a.B * a.tokens * a.n_q_heads;
   {
     const float inv = l_run > 0.f ? 1.0f / l_run : 0.f;
@@ -638,6 +659,13 @@ __global__ __launch_bounds__(64 * NWV) void attn16_kernel(AttnArgs a) {
 //  * 16-byte piece c of K row r is stored at c ^ ((r % 4) + 4 ((r / 8) % 4))
 //    and piece c of V^T row r at c ^ ((r / 4) % 4); the 16 rows one
 //    fragment read touches then fall on 16 different bank groups.
+// Bound by latency: two waves per SIMD (64 accumulator and 32 query registers
+// per 16 rows), MFMAs busy 31 % and LDS 49 % of the time at 64 streams.  The
+// softmax without a per-tile maximum and lane exchange, the fixed order of
+// reads and MFMAs, and the buffer loads to LDS (waits for single fragments)
+// took 64 streams of 500 tokens from 356 to 334 us a layer; two workgroups of
+// 4 waves per CU on two stages were slower (16 streams, 4 layers, 1625 ->
+// 1662 us), V^T stored in fragment order (no bank conflicts) within 1 %.
 template <int DH, int NWV, int NS>
 __global__ __launch_bounds__(64 * NWV) void attn16d_kernel(AttnArgs a) {
   using T = bf16_t;
@@ -653,7 +681,7 @@ __global__ __launch_bounds__(64 * NWV) void attn16d_kernel(AttnArgs a) {
   constexpr int NI = STAGE / 16 / NT;        // direct loads per thread per stage
   constexpr int LDO = DH + 8;                // output staging pitch (elements)
   static_assert(DH == 128 || DH == 256, "swizzle is laid out for 16 or 32 pieces per K row");
-  static_assert(NI * NT * 16 == STAGE && KBYTES % 1024 == 0, "stage split");
+  static_assert(NI * NT * 16 == STAGE && KBYTES == VBYTES && NWV % 2 == 0, "stage split");
   static_assert(NWV * 16 * LDO * 2 <= NS * STAGE, "output staging fits in the ring");
   extern __shared__ __attribute__((aligned(16))) T attn_ring[];
   unsigned char* ring = reinterpret_cast<unsigned char*>(attn_ring);
@@ -707,32 +735,29 @@ __global__ __launch_bounds__(64 * NWV) void attn16d_kernel(AttnArgs a) {
                    ((size_t)b * a.n_kv_heads + g) * (size_t)DH * a.S;
   const float sl2 = 1.4426950408889634f / sqrtf((float)DH);
 
-  // The thread's piece of each of its direct loads: unit u of a stage is K
-  // (row, piece) for u < KBYTES / 16, else V^T (row, piece); offsets exclude
-  // the tile's first key.  Every load instruction is all-K or all-V^T.
+  // The thread's piece of each of its direct loads, as byte offsets without
+  // the tile's first key: the first half of the waves bring K (row, piece),
+  // the others V^T (row, piece).
+  const bool isk = wave < NWV / 2;
   int off[NI];
-  bool isk[NI];
 #pragma unroll
   for (int i = 0; i < NI; ++i) {
-    const int u = 64 * (NI * wave + i) + lane;
-    isk[i] = u < KBYTES / 16;
-    if (isk[i]) {
+    const int u = 64 * (NI * (isk ? wave : wave - NWV / 2) + i) + lane;
+    if (isk) {
       const int r = u / KCH, c = (u % KCH) ^ ((r & 3) | (((r >> 3) & 3) << 2));
-      off[i] = r * DH + 8 * c;
+      off[i] = 2 * (r * DH + 8 * c);
     } else {
-      const int v = u - KBYTES / 16;
-      const int r = v >> 2, c = (v & 3) ^ ((r >> 2) & 3);
-      off[i] = r * a.S + 8 * c;
+      const int r = u >> 2, c = (u & 3) ^ ((r >> 2) & 3);
+      off[i] = 2 * (r * a.S + 8 * c);
     }
   }
+  const lds_src src = lds_source(isk ? kbase : vbase);
+  const int key_bytes = isk ? 2 * DH : 2;
   auto issue = [&](int vt, int stage) __attribute__((always_inline)) {
-    const int key0 = kts.tile(vt) * KT;
+    const int soff = kts.tile(vt) * KT * key_bytes;
     unsigned char* st = ring + stage * STAGE + 1024 * NI * wave;
 #pragma unroll
-    for (int i = 0; i < NI; ++i) {
-      const T* src = isk[i] ? kbase + (size_t)key0 * DH + off[i] : vbase + key0 + off[i];
-      lds_dma16_attn(src, st + 1024 * i);
-    }
+    for (int i = 0; i < NI; ++i) lds_dma16(src, st + 1024 * i, off[i], soff);
   };
   // fragment addresses within a stage
   const int krow = 8 * (l16 >> 2) + (l16 & 3);  // K row of A-operand row l16, half 0
@@ -748,12 +773,13 @@ __global__ __launch_bounds__(64 * NWV) void attn16d_kernel(AttnArgs a) {
   else
     wait_vmcnt_attn<0>();
   int kt = kt_begin, stage = 0;
-  bool staged = false;
+  bool redo = false;  // the tile runs again, against the raised references
+  float m_neg = kNoRef;  // minus the row's reference
   float m_pending = -INFINITY;
   while (kt < kt_end) {
     for (; kt < kt_end; ++kt) {
       const int key0 = kts.tile(kt) * KT;
-      if (!staged) {
+      if (!redo) {
         // this wave's loads of tile kt landed (later tiles may still fly) and
         // its reads of tile kt - 1 completed; after the barrier both hold for
         // every wave, so tile kt - 1's stage takes tile kt + NS - 1
@@ -765,13 +791,15 @@ __global__ __launch_bounds__(64 * NWV) void attn16d_kernel(AttnArgs a) {
         __builtin_amdgcn_s_barrier();
         if (kt + NS - 1 < kt_end) issue(kt + NS - 1, stage == 0 ? NS - 1 : stage - 1);
       }
-      staged = false;
       const unsigned char* sk = ring + stage * STAGE;
       const unsigned char* sv = sk + KBYTES;
 
       // K fragment idx = 2 ks + h and V^T fragment dt are read DK / DV ahead
-      // of their MFMA from register rings; the first V^T reads are issued
-      // before the softmax arithmetic, which hides their latency
+      // of their MFMA from register rings, the first V^T fragments after the
+      // last K fragments; the softmax arithmetic hides their latency.  Each
+      // MFMA and its read are pinned in this order: left to itself the
+      // scheduler takes the reads in an order of its own, and half of the
+      // MFMAs then wait for the read just issued.
       auto kread = [&](int idx) __attribute__((always_inline)) {
         return __builtin_bit_cast(
             bf16x8, *reinterpret_cast<const u16x8*>(sk + (krow + 4 * (idx & 1)) * (2 * DH) +
@@ -786,26 +814,20 @@ __global__ __launch_bounds__(64 * NWV) void attn16d_kernel(AttnArgs a) {
       for (int i = 0; i < DK; ++i) kf[i] = kread(i);
       f32x4 s[2][2] = {{f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}},
                        {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}}};
+      bf16x8 vf[DV];
+      static_assert(DK == DV, "one read per score MFMA");
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int idx = 0; idx < NKF; ++idx) {
         const int ks = idx >> 1, h = idx & 1;
         s[h][ks & 1] =
             __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[idx % DK], qf[ks], s[h][ks & 1], 0, 0, 0);
-        if (idx + DK < NKF) kf[idx % DK] = kread(idx + DK);
+        if (idx + DK < NKF)
+          kf[idx % DK] = kread(idx + DK);
+        else
+          vf[idx + DK - NKF] = vread(idx + DK - NKF);
+        __builtin_amdgcn_sched_barrier(0);
       }
-      bf16x8 vf[DV];
-#pragma unroll
-      for (int i = 0; i < DV; ++i) vf[i] = vread(i);
-      // issue order: DK reads, then one read (K, then the first V^T) after
-      // each score MFMA
-      static_assert(NKF - DK + DV == NKF, "one read per score MFMA");
-      __builtin_amdgcn_sched_group_barrier(0x100, DK, 0);
-#pragma unroll
-      for (int i = 0; i < NKF; ++i) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-      }
-      __builtin_amdgcn_sched_barrier(0);
       // sc[e]: key key0 + 8 lg + e
       float sc[8];
 #pragma unroll
@@ -821,50 +843,65 @@ __global__ __launch_bounds__(64 * NWV) void attn16d_kernel(AttnArgs a) {
           if (!(key < P || (key >= klo && key < khi))) sc[e] = -INFINITY;
         }
       }
-      float mt = sc[0];
-#pragma unroll
-      for (int e = 1; e < 8; ++e) mt = fmaxf(mt, sc[e]);
-      mt = max_xor16_32(mt) * sl2;
-      if (m_run == -INFINITY) m_run = mt;
-      if (__any(mt > m_run + kHeadroom)) {
-        m_pending = mt;
-        staged = true;
-        break;
-      }
-      const float m_use = m_run == -INFINITY ? 0.f : m_run;
-      float ls = 0.f;
+      // probabilities against the fixed reference (raw hardware exp2: one
+      // below 2^-126, flushed to 0, is negligible against the row's sum)
+      float ls;
       u16x8 pb;
+      auto probs = [&]() __attribute__((always_inline)) {
+        ls = 0.f;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        // raw hardware exp2: a probability below 2^-126 (flushed to 0) is
-        // negligible against the row's sum
-        const float p = __builtin_amdgcn_exp2f(fmaf(sc[e], sl2, -m_use));
-        ls += p;
-        pb[e] = f32_to_bf16(p);
+        for (int e = 0; e < 8; ++e) {
+          const float p = __builtin_amdgcn_exp2f(fmaf(sc[e], sl2, m_neg));
+          ls += p;
+          pb[e] = f32_to_bf16(p);
+        }
+      };
+      probs();
+      // some lane's share of a row sum passed the headroom (inf while the row
+      // has no reference)
+      if (!redo && __any(!(ls <= kSumLimit))) {
+        float mt = sc[0];
+#pragma unroll
+        for (int e = 1; e < 8; ++e) mt = fmaxf(mt, sc[e]);
+        mt = max_xor16_32(mt) * sl2;
+        if (m_run == -INFINITY) {  // the row's first keys: nothing to rescale
+          m_run = mt;
+          m_neg = mt == -INFINITY ? kNoRef : -mt;
+        }
+        if (__any(mt > m_run + kRaise)) {
+          m_pending = mt;
+          redo = true;
+          break;
+        }
+        probs();
       }
-      l_run += sum_xor16_32(ls);
+      redo = false;
+      l_run += ls;
       const bf16x8 pf = __builtin_bit_cast(bf16x8, pb);
       // O^T (dh x queries) += V^T P^T: dh row 16 dt + l16, keys 8 lg .. 8 lg + 7
 #pragma unroll
       for (int dt = 0; dt < NDT; ++dt) {
         acc[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[dt % DV], pf, acc[dt], 0, 0, 0);
         if (dt + DV < NDT) vf[dt % DV] = vread(dt + DV);
+        __builtin_amdgcn_sched_barrier(0);
       }
       stage = stage + 1 == NS ? 0 : stage + 1;
     }
-    if (staged) {
-      const float m_new = m_pending > m_run + kHeadroom ? m_pending : m_run;
+    if (redo) {
+      const float m_new = m_pending > m_run + kRaise ? m_pending : m_run;
       const float alpha = m_run == -INFINITY ? 0.f : exp2f(m_run - m_new);
       l_run *= alpha;
 #pragma unroll
       for (int dt = 0; dt < NDT; ++dt) acc[dt] *= alpha;
       m_run = m_new;
+      m_neg = m_run == -INFINITY ? kNoRef : -m_run;
     }
   }
 
   // Normalised output through LDS (the ring, free once every wave is past
   // its last tile): lane (query l16, group lg) holds dh 16 dt + 4 lg + 0..3;
   // rows then go out whole, 16 bytes per lane.
+  l_run = sum_xor16_32(l_run);
   const size_t R = (size_t)a.B * a.tokens * a.n_q_heads;
   __syncthreads();
   T* so = attn_ring + wave * 16 * LDO;

@@ -109,6 +109,23 @@ __host__ __device__ __forceinline__ size_t tile_off(int row, int k, int K) {
          (k % (4 * E)) / E * (16 * E) + (row & 15) * E + k % E;
 }
 
+// Direct-to-LDS loads: lane l's 16 bytes at byte base + voff + soff go to
+// lds + 16 l (lds and soff uniform over the wave).  Buffer loads, not
+// global_load_lds: the compiler counts the latter as flat accesses that may
+// return through the LDS counter, and every wait for a fragment read in a loop
+// that issues one becomes a wait for all of them (lgkmcnt(0)).  They also take
+// one 32-bit offset register per piece instead of a 64-bit address.
+// (Plain functions: such a builtin written directly in a kernel template body
+// loses the template's host-side launch stub.)
+typedef __amdgpu_buffer_rsrc_t lds_src;
+__device__ __forceinline__ lds_src lds_source(const void* base) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, 0x7fffffff, 0x00020000);
+}
+__device__ __forceinline__ void lds_dma16(lds_src src, void* lds, int voff, int soff) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(src, (__attribute__((address_space(3))) void*)lds, 16,
+                                           voff, soff, 0, 0);
+}
+
 // Sum over the 64 lanes, the same value in every lane, without LDS
 // permutes: the gfx950 lane swaps exchange across 32-lane halves and 16-lane
 // rows; DPP row rotations by 8 and 4 and quad permutes (xor 2, xor 1) finish
