@@ -1142,7 +1142,17 @@ GemmPlan plan_tiles(int M, int N, int K, bool bf16, bool reduce_fused) {
     if (reduce_fused && bf16 && ntiles(T128x128w8) >= 96)
       p.tile = T128x128w8;
     else
-      p.tile = ntiles(T128x128w8) >= 200 ? T128x128w8 : T64x128w4;
+      // 128x128 from 200 tiles on, except narrow products whose 64x128 tiles
+      // fit one round of two workgroups per CU, so that one's long epilogue
+      // runs over the other's main loop (QKV at 1155 rows, 200 and 380 tiles:
+      // 4-layer pass 566 -> 552 us; gate/up at 500 rows, 256 and 512 tiles,
+      // is faster on 128x128: 13.8 us against 17.3).  N > K leaves out the
+      // projections back to the width (8 streams of 500 tokens: 1020 us on
+      // 128x128 tiles, 1067 on 64x128)
+      p.tile = ntiles(T128x128w8) >= 200 &&
+                       !(bf16 && N > K && N <= 4096 && ntiles(T64x128w4) <= 512)
+                   ? T128x128w8
+                   : T64x128w4;
   } else if (M > 32) {
     p.tile = T64x128w4;
   } else {
@@ -1153,6 +1163,13 @@ GemmPlan plan_tiles(int M, int N, int K, bool bf16, bool reduce_fused) {
   if ((p.tiles < 128 || (reduce_fused && p.tiles <= 160)) && p.tile != T256x256big)
     while ((long)p.tiles * p.ks * 2 <= 320 && nk / (p.ks * 2) >= 4 && p.ks < 8) p.ks *= 2;
   p.ws_floats = p.ks > 1 ? (size_t)p.ks * M * N : 0;
+  // Where the splits need a reduction kernel of their own (5-7 us), bf16
+  // splits under 32 k-tiles (0.45 us each) lose: QKV at 384 rows and 12
+  // k-tiles took 7.5 + 7.2 us split in two; 4 layers, 3 streams of 128
+  // tokens, 268 -> 252 us unsplit (fp32, 1.2 us a k-tile, keeps them: 416 us
+  // against 452).  The workspace still counts them, so that
+  // fv_decode_step_noalloc accepts the same steps.
+  if (bf16 && !reduce_fused && nk < 32) p.ks = 1;
   return p;
 }
 
