@@ -364,7 +364,6 @@ void launch_seq_euler(float* x, const float* v, const float* tsched, int j, int 
 void launch_cold_start(float* buffer, uint64_t* noise_state, int* n_valid, int b0, int nb, int K,
                        int CA, hipStream_t s);
 void launch_copy_f32(float* dst, const float* src, size_t n, hipStream_t s);
-void launch_fill_t(float* t, const float* tsched, int j, int B, hipStream_t s);
 template <typename T>
 void launch_prefix_copy(const T* k, const T* v, int L, int B, int src_batch, int ld, int Hkv,
                         int dh, T* karena, T* vtarena, int Bmax, int S, const int* len,
@@ -425,6 +424,10 @@ int attention_row_tiles(int tokens, int n_q_heads, int n_kv_heads);
 template <typename T>
 hipError_t attention_prepare();
 
+// Euler steps of a sequential decode whose FiLM maps are computed together:
+// the most rows the weight-streaming FiLM product takes.
+constexpr int kSeqRows = 16;
+
 // ------------------------------------------------------------------- handle
 struct GraphEntry {
   int kind = 0, batch = 0, n = 0, slot = 0;
@@ -475,7 +478,10 @@ struct Handle {
   void* m = nullptr;                                              // T [Bmax*T][F]
   float* v = nullptr;                                             // [Bmax][K][C][A]
   void* part_o = nullptr; float* part_ml = nullptr; int max_split = 1;
-  float* seq_x = nullptr; float* seq_t = nullptr;
+  float* seq_x = nullptr;
+  void* seq_act = nullptr;      // T [3][kSeqRows][W]: embedding, hidden, condition rows of Euler steps
+  float* seq_mod = nullptr;     // [kSeqRows][Nmod] their FiLM maps
+  int* d_one = nullptr;         // holds 1: every stream reads the step's one row (film_row)
   std::vector<std::pair<int, float*>> tscheds;  // sequential-decode t_j tables by step count
 
   GemmWork gw;                    // split-K workspace and counters

@@ -985,12 +985,6 @@ __global__ void copy_f32_kernel(float* __restrict__ d, const float* __restrict__
   if (i < n) d[i] = s[i];
 }
 
-__global__ void fill_t_kernel(float* __restrict__ t, const float* __restrict__ tsched, int j,
-                              int B) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < B) t[i] = tsched[j];
-}
-
 // ---------------------------------------------------------- prefix install
 // k: [L][B][ld][Hkv][dh] -> karena [L][Bmax][Hkv][S][dh], rows p < len[b];
 // v: same source layout -> vtarena [L][Bmax][Hkv][dh][S] through a 64x64 LDS
@@ -1161,10 +1155,6 @@ void launch_seq_euler(float* x, const float* v, const float* tsched, int j, int 
 void launch_copy_f32(float* dst, const float* src, size_t n, hipStream_t s) {
   hipLaunchKernelGGL(copy_f32_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, dst,
                      src, n);
-}
-
-void launch_fill_t(float* t, const float* tsched, int j, int B, hipStream_t s) {
-  hipLaunchKernelGGL(fill_t_kernel, dim3((B + 255) / 256), dim3(256), 0, s, t, tsched, j, B);
 }
 
 template <typename T>
