@@ -430,9 +430,12 @@ __global__ __launch_bounds__(64 * NW) void gemm_dma_kernel(const bf16_t* __restr
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave % WGM, wn = wave / WGM;
-  int tm, tn;
-  int kz;
+  int tm, tn, kz;
   tile_of(tm, tn, kz);
+  // uniform, though divided in vector registers: scalar from here on
+  tm = __builtin_amdgcn_readfirstlane(tm);
+  tn = __builtin_amdgcn_readfirstlane(tn);
+  kz = __builtin_amdgcn_readfirstlane(kz);
   const int m0 = tm * BM, n0 = tn * BN;
   const int nk_all = K / BK;
   const int kt0 = (kz * nk_all) / KS, kt1 = ((kz + 1) * nk_all) / KS;
@@ -677,9 +680,60 @@ struct EpiBiasF32 {
 template <typename T>
 struct EpiQkv {
   QkvArgs<T> a;
+  // The query columns of rows of at most two streams, the bulk of the product
+  // (rows from row_hi on are the second stream's; pos_lo and pos_hi: rotary
+  // position minus row of each).  Table and output addresses are a uniform
+  // base and a 32-bit lane offset that moves by uniform steps from row to
+  // row: with an address of its own per element the epilogue took as many
+  // VALU cycles as the 1024-deep product takes MFMA cycles (3900 instructions
+  // a wave at 32000 rows; with it, 64 streams of 500 tokens, 2 layers, 3047 ->
+  // 3000 us, batch 1 of 18 layers 1375 -> 1367).  Rows past M read a clamped
+  // table entry and are not stored.
+  __device__ __forceinline__ void rotate_q(const f32x16& v0, const f32x16& v1, int row0, int c0,
+                                           int lane, int M, int row_hi, int pos_lo,
+                                           int pos_hi) const {
+    const int dh = a.head_dim, half = dh / 2, qd = a.n_q_heads * dh;
+    const int head = c0 / dh, dlo = 32 * ((c0 - head * dh) >> 6) + (lane & 31);
+    const int lrow = 4 * (lane >> 5), k4 = lane & 3;
+    const char* __restrict__ rcos = reinterpret_cast<const char*>(a.rcos);
+    const char* __restrict__ rsin = reinterpret_cast<const char*>(a.rsin);
+    const int step = 4 * half;  // bytes of a table row
+    const int off_lo = pos_lo * step, off_hi = pos_hi * step;
+    const uint32_t off_max = (uint32_t)a.S * step - 4;
+    const int lane_off = (row0 + lrow) * step + 4 * dlo;
+    float cs[16], sn[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int ro = 8 * (r >> 2) + (r & 3);
+      const uint32_t off = min(
+          (uint32_t)(lane_off + ro * step + (lrow >= row_hi - row0 - ro ? off_hi : off_lo)), off_max);
+      cs[r] = *reinterpret_cast<const float*>(rcos + off);
+      sn[r] = *reinterpret_cast<const float*>(rsin + off);
+    }
+    T* qb = a.q + (size_t)row0 * qd + head * dh;  // uniform
+    const uint32_t lo = (uint32_t)((lrow + k4) * qd + (dlo & ~3));
+#pragma unroll
+    for (int q4 = 0; q4 < 4; ++q4) {
+      float y0[4], y1[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int r = 4 * q4 + e;
+        y0[e] = v0[r] * cs[r] - v1[r] * sn[r];
+        y1[e] = v1[r] * cs[r] + v0[r] * sn[r];
+      }
+      const f32x4 u0 = quad_rows(y0[0], y0[1], y0[2], y0[3], lane);
+      const f32x4 u1 = quad_rows(y1[0], y1[1], y1[2], y1[3], lane);
+      if (row0 + 8 * q4 + lrow + k4 >= M) continue;
+      T* dst = qb + (size_t)8 * q4 * qd + lo;
+      store4<T>(dst, u0[0], u0[1], u0[2], u0[3]);
+      store4<T>(dst + half, u1[0], u1[1], u1[2], u1[3]);
+    }
+  }
   template <int FM, int FN>
   __device__ void apply(f32x16 (&acc)[FM][FN], int row0, int col0, int lane, int M) const {
     static_assert(FN % 2 == 0, "QKV epilogue needs column pairs");
+    row0 = __builtin_amdgcn_readfirstlane(row0);  // a wave's rows and columns
+    col0 = __builtin_amdgcn_readfirstlane(col0);
     const int dh = a.head_dim, half = dh / 2;
     const int qd = a.n_q_heads * dh, kd = a.n_kv_heads * dh;
     const float* __restrict__ rcos = a.rcos;
@@ -690,7 +744,8 @@ struct EpiQkv {
     // per-row lookup ahead of the rotary tables); otherwise every row looks
     // its stream up.
     const int ntok = a.tokens;
-    const int b_lo = min(row0, M - 1) / ntok, b_hi = min(row0 + 32 * FM - 1, M - 1) / ntok;
+    const int b_lo = __builtin_amdgcn_readfirstlane(min(row0, M - 1) / ntok);
+    const int b_hi = __builtin_amdgcn_readfirstlane(min(row0 + 32 * FM - 1, M - 1) / ntok);
     const bool two = b_hi - b_lo <= 1;
     const int len_lo = buffer_row0(a.len[b_lo]), len_hi = buffer_row0(a.len[b_hi]);
     const int gap_lo = len_lo - a.len[b_lo], gap_hi = len_hi - a.len[b_hi];
@@ -713,12 +768,17 @@ struct EpiQkv {
     };
 #pragma unroll
     for (int i = 0; i < FM; ++i) {
-      int2 rp[16];
-#pragma unroll
-      for (int r = 0; r < 16; ++r) rp[r] = locate(row0 + 32 * i + acc_row(r, lane));
 #pragma unroll
       for (int j = 0; j < FN; j += 2) {
         const int c0 = col0 + 32 * j;  // first packed column of the pair group
+        if (two && c0 < qd) {
+          rotate_q(acc[i][j], acc[i][j + 1], row0 + 32 * i, c0, lane, M, row_hi,
+                   a.len[b_lo] - b_lo * ntok, a.len[b_hi] - b_hi * ntok);
+          continue;
+        }
+        int2 rp[16];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) rp[r] = locate(row0 + 32 * i + acc_row(r, lane));
         if (c0 < qd + kd) {
           const bool isq = c0 < qd;
           const int cc = isq ? c0 : c0 - qd;

@@ -118,8 +118,15 @@ __host__ __device__ __forceinline__ size_t tile_off(int row, int k, int K) {
 // (Plain functions: such a builtin written directly in a kernel template body
 // loses the template's host-side launch stub.)
 typedef __amdgpu_buffer_rsrc_t lds_src;
+// The base is the same in every lane of the wave; where it comes out of vector
+// arithmetic (a tile index by integer division) the compiler does not know,
+// and wraps every load in a loop over the lanes' descriptors.
 __device__ __forceinline__ lds_src lds_source(const void* base) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, 0x7fffffff, 0x00020000);
+  const uint64_t p = reinterpret_cast<uint64_t>(base);
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((int)(uint32_t)p);
+  const uint32_t hi = __builtin_amdgcn_readfirstlane((int)(uint32_t)(p >> 32));
+  return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>((uint64_t)hi << 32 | lo), 0,
+                                           0x7fffffff, 0x00020000);
 }
 __device__ __forceinline__ void lds_dma16(lds_src src, void* lds, int voff, int soff) {
   __builtin_amdgcn_raw_ptr_buffer_load_lds(src, (__attribute__((address_space(3))) void*)lds, 16,
