@@ -1192,7 +1192,9 @@ GemmPlan plan_tiles(int M, int N, int K, bool bf16, bool reduce_fused) {
   // slower at batch 44 (88) and 48 (120).  Two full rounds are best on
   // 256x256 tiles, also below 4096 rows (4000 rows, gate/up 83.6 -> 73.1 us).
   const long n256 = ntiles(T256x256big);
-  if (bf16 && M >= 2048 && N % 256 == 0 && n256 >= 200 && !(n256 > 256 && n256 < 328)) {
+  if (bf16 && K >= 1 << 22) {
+    p.tile = T32x128w2;  // the direct-to-LDS tiles' byte offsets (512 K) are 32-bit
+  } else if (bf16 && M >= 2048 && N % 256 == 0 && n256 >= 200 && !(n256 > 256 && n256 < 328)) {
     p.tile = T256x256big;
   } else if (M >= 4096) {
     p.tile = bf16 && N % 256 == 0 ? T128x128w8 : T256x128w8;
