@@ -346,8 +346,9 @@ fv_status fv_set_graph_mode(fv_handle h, int32_t enabled);
  *  FV_QUERY_DEVICE_BYTES: device memory the handle holds (weights, prefix
  *    arenas, scratch, workspace), in bytes; `batch` is ignored;
  *  FV_QUERY_NOALLOC_SCRATCH_BYTES: static scratch fv_decode_step_noalloc
- *    needs for a step at batch `batch` (accepted when at most
- *    FV_NOALLOC_SCRATCH_BYTES);
+ *    asks for at batch `batch` when it is given t (a step is accepted when
+ *    this is at most FV_NOALLOC_SCRATCH_BYTES; one with the installed
+ *    schedule computes no FiLM maps and may ask for less);
  *  FV_QUERY_OUT_PROJ_SPLITS: split-K factor of the output projection at batch
  *    `batch` (1: unsplit, the gated residual runs in the GEMM's epilogue;
  *    more: split partials reduced with the residual and the next norm).

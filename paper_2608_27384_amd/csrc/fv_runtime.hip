@@ -615,14 +615,22 @@ StepScratch scratch_of(const Handle* h, int B, int s, Plan plan) {
   for (const GemmPlan& p : ps) r.ws = std::max(r.ws, round256(p.ws_floats * 4));
   return r;
 }
-StepScratch step_scratch(const Handle* h, int B) {
-  return scratch_of(h, B, attn_split(h, B), plan_gemm);
+// film: the step computes its FiLM maps (no schedule), which several streams
+// do in two products, of K and of (B - 1) K rows (enqueue_film_maps); fewer
+// rows may be split further than B K.
+StepScratch step_scratch(const Handle* h, int B, bool film) {
+  StepScratch r = scratch_of(h, B, attn_split(h, B), plan_gemm);
+  if (film && B > 1)
+    for (int rows : {h->K, (B - 1) * h->K})
+      for (int N : {h->W, h->Nmod})
+        r.ws = std::max(r.ws, round256(plan_gemm(rows, N, h->W, h->bf16).ws_floats * 4));
+  return r;
 }
 // What fv_decode_step_noalloc asks for: the step's scratch, and at least the
 // tile kernels' plan of it with 512 attention workgroups, so that the steps
 // it refuses do not depend on which kernels a row count takes.
-size_t noalloc_bytes(const Handle* h, int B) {
-  return std::max(step_scratch(h, B).total(),
+size_t noalloc_bytes(const Handle* h, int B, bool film) {
+  return std::max(step_scratch(h, B, film).total(),
                   scratch_of(h, B, attn_split_for(h, B, 512), plan_tiles).total());
 }
 
@@ -1108,8 +1116,8 @@ fv_status fv_decode_step_noalloc(fv_handle h, float* buffer, const float* t, flo
     if (overlap(buffer, nbuf, out_chunk, nout)) fail(FV_ERR_INVALID_ARG, "buffer and out_chunk overlap");
     const float* tt = schedule_or(h, t, B);
     const float* mod = t ? nullptr : h->mod_cache;
-    const StepScratch need = step_scratch(h, B);
-    const size_t asked = noalloc_bytes(h, B);
+    const StepScratch need = step_scratch(h, B, t != nullptr);
+    const size_t asked = noalloc_bytes(h, B, t != nullptr);
     if (asked > kStaticScratchBytes)
       fail(FV_ERR_INVALID_ARG, "a step at batch " + std::to_string(B) + " needs " +
                                    std::to_string(asked) +
@@ -1387,7 +1395,7 @@ fv_status fv_query(fv_handle h, int32_t what, int32_t batch, int64_t* value) {
         break;
       case FV_QUERY_NOALLOC_SCRATCH_BYTES:
         if (batch < 1 || batch > h->Bmax) fail(FV_ERR_INVALID_ARG, "batch outside 1..max_batch");
-        *value = (int64_t)noalloc_bytes(h, batch);
+        *value = (int64_t)noalloc_bytes(h, batch, true);
         break;
       default:
         fail(FV_ERR_INVALID_ARG, "unknown query");

@@ -102,3 +102,32 @@ def test_noalloc_rejects_a_step_larger_than_the_array():
             ref.close()
     finally:
         case.close()
+
+
+def test_noalloc_counts_the_film_products_of_several_streams():
+    """Streams at noise levels of their own compute their FiLM maps in
+    products of K and (batch - 1) K rows, which the plan may split where one of
+    batch K rows is not: at width 896 in fp32, time-MLP products of 4600 rows
+    in 2 splits of 33 MB together, of 4800 rows unsplit.  With t the step asks
+    for them and is refused; with a schedule it computes none and runs."""
+    w = synth.Workload("noalloc_film", n_layers=1, width=896, n_q_heads=2, n_kv_heads=1,
+                       head_dim=64, mlp_dim=128, action_dim=8, chunk_len=4, n_chunks=200,
+                       prefix_len=8, batch=24, dtype=synth.FP32)
+    a, r = Case(w, noise_seed=2), Case(w, noise_seed=2)
+    try:
+        assert a.ex.noalloc_scratch_bytes(24) >= 2 * 23 * 200 * 896 * 4
+        st = fvb.lib().fv_decode_step_noalloc(a.ex.handle, a.xd.data_ptr(), a.td.data_ptr(),
+                                              a.out.data_ptr(), _stream())
+        assert st == fvb.FV_ERR_INVALID_ARG
+        for c in (a, r):
+            c.ex.set_schedule(c.td)
+            c.td = None
+        st = fvb.lib().fv_decode_step_noalloc(a.ex.handle, a.xd.data_ptr(), None,
+                                              a.out.data_ptr(), _stream())
+        assert st == fvb.FV_OK, fvb.lib().fv_last_error(a.ex.handle)
+        r.ex.decode_step(r.xd, None, r.out)
+        assert np.array_equal(host(a.out), host(r.out))
+        assert np.array_equal(host(a.xd), host(r.xd))
+    finally:
+        a.close()
+        r.close()
