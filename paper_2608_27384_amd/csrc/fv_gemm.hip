@@ -223,7 +223,9 @@ __global__ __launch_bounds__(64 * NW * KG) void gemm_kernel(const T* __restrict_
   }
 
   // offset of k for piece p: the weights' tiles put 16 rows' k side by side
-  auto koff = [](int p, int k) __attribute__((always_inline)) { return p < NA ? k : 16 * k; };
+  auto koff = [](int p, int k) __attribute__((always_inline)) {
+    return p < NA ? (size_t)k : tile_k(k);
+  };
 
   // Prologue: stage kt0 into LDS buffer 0, stage kt0+1 into registers.
   u32x4 rg[NP];

@@ -108,6 +108,9 @@ __host__ __device__ __forceinline__ size_t tile_off(int row, int k, int K) {
   return ((size_t)(row >> 4) * (K / (4 * E)) + k / (4 * E)) * (64 * E) +
          (k % (4 * E)) / E * (16 * E) + (row & 15) * E + k % E;
 }
+// What k, a multiple of a tile's 64 bytes, adds to tile_off: 64-bit, past 2^31
+// from k = 2^27 on.
+__host__ __device__ __forceinline__ size_t tile_k(int k) { return (size_t)16 * k; }
 
 // Direct-to-LDS loads: lane l's 16 bytes at byte base + voff + soff go to
 // lds + 16 l (lds and soff uniform over the wave).  Buffer loads, not
