@@ -6,9 +6,9 @@
 //
 // Two main loops.  The bf16 tiles 256x256, 128x128 and 64x128 use
 // gemm_dma_kernel: k-tiles go from memory straight into a ring of LDS stages
-// with the direct-to-LDS loads (see there).  The fp32 tiles and the small-M
-// 32x128 tile use gemm_kernel, described here, and M <= 16 time-MLP layers a
-// GEMV.
+// with the direct-to-LDS loads (see there).  The fp32 tiles, the bf16 256x128
+// tile and bf16 products of 2^22 k or more use gemm_kernel, described here.
+// Products of at most 64 rows have kernels of their own (fv_few.hip).
 //
 // gemm_kernel block: NW waves (2, 4 or 8).  Tile BM x BN; k is staged through
 // LDS 128 bytes per row (64 bf16 / 32 fp32) at a time in two buffers.  While a wave
@@ -46,6 +46,7 @@
 // Paired epilogues rely on the weight packing: columns [64p, 64p+32) and
 // [64p+32, 64p+64) of a packed matrix hold the two partners of a pair, which
 // then sit in the same lane and register of two adjacent 32-column tiles.
+#include <stdexcept>
 #include <type_traits>
 
 #include "fv_internal.h"
@@ -165,14 +166,14 @@ struct EpiSkip<Epi, std::void_t<decltype(&Epi::skipped)>> {
   __device__ static bool skip(const Epi& e) { return e.skipped(); }
 };
 
-template <typename T, int BM, int BN, int NW, int WGM, int KG, class Epi>
-__global__ __launch_bounds__(64 * NW * KG) void gemm_kernel(const T* __restrict__ A,
-                                                            const T* __restrict__ Bt, int M,
-                                                            int N, int K, int KS,
-                                                            float* __restrict__ ws, Epi epi) {
+template <typename T, int BM, int BN, int NW, int WGM, class Epi>
+__global__ __launch_bounds__(64 * NW) void gemm_kernel(const T* __restrict__ A,
+                                                       const T* __restrict__ Bt, int M, int N,
+                                                       int K, int KS, float* __restrict__ ws,
+                                                       Epi epi) {
   if (EpiSkip<Epi>::skip(epi)) return;
   using MF = Mf32<T>;
-  constexpr int NT = 64 * NW * KG;
+  constexpr int NT = 64 * NW;
   constexpr int WGN = NW / WGM;
   constexpr int WTM = BM / WGM, WTN = BN / WGN;
   constexpr int FM = WTM / 32, FN = WTN / 32;
@@ -181,17 +182,12 @@ __global__ __launch_bounds__(64 * NW * KG) void gemm_kernel(const T* __restrict_
   constexpr int LDR = BK + EPV;             // LDS row pitch (one vector of padding)
   constexpr int NA = BM * 8 / NT, NB = BN * 8 / NT, NP = NA + NB;  // 16-byte pieces per thread
   constexpr int NSTEP = BK / MF::KM;        // k-steps per stage
-  constexpr int NSG = NSTEP / KG;           // k-steps of a stage per wave group
   static_assert(FM >= 1 && FN >= 1 && WGM * WGN == NW, "bad tile");
-  static_assert((BM * 8) % NT == 0 && (BN * 8) % NT == 0 && NSG % 2 == 0, "bad tile");
-  static_assert(KG == 1 || NW * FM * FN * 4096 <= 2 * (BM + BN) * LDR * (int)sizeof(T),
-                "k-group reduction does not fit the staging buffers");
-
+  static_assert((BM * 8) % NT == 0 && (BN * 8) % NT == 0 && NSTEP % 2 == 0, "bad tile");
   __shared__ __attribute__((aligned(16))) T sm[2 * (BM + BN) * LDR];  // [buf][A rows ; B rows]
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int kg = wave / NW, wv = wave - kg * NW;  // k-group; wave within the group
-  const int wm = wv % WGM, wn = wv / WGM;
+  const int wm = wave % WGM, wn = wave / WGM;
   int tm, tn, kz;
   tile_of(tm, tn, kz);
   const int m0 = tm * BM, n0 = tn * BN;
@@ -242,14 +238,10 @@ __global__ __launch_bounds__(64 * NW * KG) void gemm_kernel(const T* __restrict_
 
   // Fragments are double-buffered: those of k-step ks+1 are read while the
   // MFMAs of k-step ks run.  The next stage's register pieces go to the
-  // other LDS buffer during a group's k-steps 0..NSG-2 (each freed register
-  // then loads its piece of the stage after that); one barrier, placed
-  // before the group's last k-step, publishes the new stage, whose first
-  // fragments are read while the last k-step's MFMAs run.  With KG = 2 the
-  // two wave groups take the first and second half of every stage's k-steps
-  // on the same output tile (twice the waves per CU, and so twice the LDS
-  // requests in flight, for the same LDS bytes) and their accumulators are
-  // summed through LDS at the end.
+  // other LDS buffer during k-steps 0..NSTEP-2 (each freed register then
+  // loads its piece of the stage after that); one barrier, placed before the
+  // last k-step, publishes the new stage, whose first fragments are read
+  // while the last k-step's MFMAs run.
   const int lr = lane & 31, lk = MF::KG * (lane >> 5);
   typename MF::frag af[2][FM], bfr[2][FN];
   auto read_frags = [&](int slot, int buf, int ks) __attribute__((always_inline)) {
@@ -259,20 +251,19 @@ __global__ __launch_bounds__(64 * NW * KG) void gemm_kernel(const T* __restrict_
 #pragma unroll
     for (int j = 0; j < FN; ++j) bfr[slot][j] = MF::load(base + (brow + 32 * j + lr) * LDR);
   };
-  const int s0 = kg * NSG;
-  read_frags(0, 0, s0);
+  read_frags(0, 0, 0);
   for (int kt = kt0; kt < kt1; ++kt) {
     const int cur = (kt - kt0) & 1;
     const int knext = min((kt + 2) * BK, klast);  // unconditional prefetch (clamped)
     T* const nxt = sm + (cur ^ 1) * (BM + BN) * LDR;
 #pragma unroll
-    for (int ks = 0; ks < NSG; ++ks) {
+    for (int ks = 0; ks < NSTEP; ++ks) {
       const int cb = ks & 1;
-      if (ks + 1 < NSG) {
-        read_frags(cb ^ 1, cur, s0 + ks + 1);
+      if (ks + 1 < NSTEP) {
+        read_frags(cb ^ 1, cur, ks + 1);
       } else {
         __syncthreads();
-        read_frags(cb ^ 1, cur ^ 1, s0);
+        read_frags(cb ^ 1, cur ^ 1, 0);
       }
 #pragma unroll
       for (int i = 0; i < FM; ++i)
@@ -281,7 +272,7 @@ __global__ __launch_bounds__(64 * NW * KG) void gemm_kernel(const T* __restrict_
       int nw = 0;
 #pragma unroll
       for (int p = 0; p < NP; ++p) {
-        if (ks + 1 == NSG || (p * (NSG - 1)) / NP != ks) continue;
+        if (ks + 1 == NSTEP || (p * (NSTEP - 1)) / NP != ks) continue;
         *reinterpret_cast<u32x4*>(&nxt[lp[p]]) = rg[p];
         rg[p] = *reinterpret_cast<const u32x4*>(gp[p] + koff(p, knext));
         ++nw;
@@ -306,40 +297,6 @@ __global__ __launch_bounds__(64 * NW * KG) void gemm_kernel(const T* __restrict_
       for (int q = 0; q < FM * FN; ++q)
         if (q >= nrd + nw) __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
     }
-  }
-  if constexpr (KG > 1) {
-    // group kg > 0 hands its sums to group 0 through the (now idle) staging
-    // buffers: [wave][i][j][register quad][lane][4], 16 bytes per lane
-    __syncthreads();
-    f32x4* red = reinterpret_cast<f32x4*>(sm);
-    for (int g = 1; g < KG; ++g) {
-      if (kg == g) {
-#pragma unroll
-        for (int i = 0; i < FM; ++i)
-#pragma unroll
-          for (int j = 0; j < FN; ++j)
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-              red[(((wv * FM + i) * FN + j) * 4 + q) * 64 + lane] =
-                  f32x4{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2],
-                        acc[i][j][4 * q + 3]};
-      }
-      __syncthreads();
-      if (kg == 0) {
-#pragma unroll
-        for (int i = 0; i < FM; ++i)
-#pragma unroll
-          for (int j = 0; j < FN; ++j)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-              const f32x4 v = red[(((wv * FM + i) * FN + j) * 4 + q) * 64 + lane];
-#pragma unroll
-              for (int e = 0; e < 4; ++e) acc[i][j][4 * q + e] += v[e];
-            }
-      }
-      if (g + 1 < KG) __syncthreads();
-    }
-    if (kg != 0) return;
   }
   const int ar = wm * WTM, bc = wn * WTN;
 
@@ -1070,21 +1027,16 @@ void launch_stream_bias_f32(const bf16_t* A, const bf16_t* Bt, const float* bias
 // Tile shapes (BM x BN, waves); every wave owns a sub-tile at least 64
 // columns wide, so paired epilogues find both partners of a 64-column pair
 // group in one wave.
-enum Tile { T256x128w8 = 0, T128x128w8 = 1, T64x128w4 = 2, T32x128w2 = 3, T256x256big = 4,
-            TFew = 5 };
-constexpr int kTileBM[] = {256, 128, 64, 32, 256};
-constexpr int kTileBN[] = {128, 128, 128, 128, 256};
-// k-groups per tile (waves per block = NW x KG): the 2-wave 32-row tile
-// (M <= 32: weight-streaming GEMMs) gets a second wave group, doubling the
-// loads and LDS reads in flight; the larger tiles measured no gain.
-constexpr int kTileKG[] = {1, 1, 1, 2};
+enum Tile { T256x128w8 = 0, T128x128w8 = 1, T64x128w4 = 2, T256x256big = 3, TFew = 4 };
+constexpr int kTileBM[] = {256, 128, 64, 256};
+constexpr int kTileBN[] = {128, 128, 128, 256};
 
-template <typename T, int BM, int BN, int NW, int WGM, int KG, class Epi>
+template <typename T, int BM, int BN, int NW, int WGM, class Epi>
 void launch_tile(const T* A, const T* Bt, int M, int N, int K, const GemmPlan& p,
                  const GemmWork& w, const Epi& epi, hipStream_t s) {
   dim3 grid(N / BN, (M + BM - 1) / BM, p.ks);
-  hipLaunchKernelGGL((gemm_kernel<T, BM, BN, NW, WGM, KG, Epi>), grid, dim3(64 * NW * KG), 0, s,
-                     A, Bt, M, N, K, p.ks, w.ws, epi);
+  hipLaunchKernelGGL((gemm_kernel<T, BM, BN, NW, WGM, Epi>), grid, dim3(64 * NW), 0, s, A, Bt, M,
+                     N, K, p.ks, w.ws, epi);
   if (p.ks > 1 && !std::is_same<Epi, EpiNone>::value)
     hipLaunchKernelGGL((gemm_reduce_kernel<BM, BN, NW, WGM, Epi>), dim3(grid.x, grid.y),
                        dim3(64 * NW), 0, s, w.ws, M, N, p.ks, epi);
@@ -1117,45 +1069,38 @@ void launch_dma(const bf16_t* A, const bf16_t* Bt, int M, int N, int K, const Ge
                          dim3(64 * NW), 0, s, w.ws, M, N, p.ks, epi);
 }
 
-// Launches tile p.tile with the direct-to-LDS kernel when it has one;
-// returns false otherwise.  The 128x128 tile takes three stages when the
-// grid fits the chip with one workgroup per CU (the deeper ring hides load
-// latency, measured 1568 against 1864 us per batch-1 step with two), two
-// stages otherwise (two workgroups then fit per CU and overlap each other).
-template <class Epi>
-bool try_dma(const bf16_t* A, const bf16_t* Bt, int M, int N, int K, const GemmPlan& p,
-             const GemmWork& w, const Epi& epi, hipStream_t s) {
-  const bool rounds = (long)p.tiles * p.ks > 256;
-  switch (p.tile) {
-    case T256x256big: launch_dma<256, 256, 8, 2, 2>(A, Bt, M, N, K, p, w, epi, s); return true;
-    case T128x128w8:
-      if (rounds)
-        launch_dma<128, 128, 8, 4, 2>(A, Bt, M, N, K, p, w, epi, s);
-      else
-        launch_dma<128, 128, 8, 4, 3>(A, Bt, M, N, K, p, w, epi, s);
-      return true;
-    case T64x128w4:  // chosen only below about 400 tiles x splits: one round
-      launch_dma<64, 128, 4, 2, 3>(A, Bt, M, N, K, p, w, epi, s);
-      return true;
-    default: return false;
+// Launches the tile kernel of plan p (not TFew).  The 128x128 tile of the
+// direct-to-LDS kernel takes three stages when the grid fits the chip with one
+// workgroup per CU (the deeper ring hides load latency, measured 1568 against
+// 1864 us per batch-1 step with two), two stages otherwise (two workgroups
+// then fit per CU and overlap each other).
+template <typename T, class Epi>
+void run_tile(const T* A, const T* Bt, int M, int N, int K, const GemmPlan& p, const GemmWork& w,
+              const Epi& epi, hipStream_t s) {
+  if constexpr (sizeof(T) == 2) {
+    if (p.dma) {
+      const bool rounds = (long)p.tiles * p.ks > 256;
+      switch (p.tile) {
+        case T256x256big: return launch_dma<256, 256, 8, 2, 2>(A, Bt, M, N, K, p, w, epi, s);
+        case T128x128w8:
+          return rounds ? launch_dma<128, 128, 8, 4, 2>(A, Bt, M, N, K, p, w, epi, s)
+                        : launch_dma<128, 128, 8, 4, 3>(A, Bt, M, N, K, p, w, epi, s);
+        case T64x128w4: return launch_dma<64, 128, 4, 2, 3>(A, Bt, M, N, K, p, w, epi, s);
+      }
+    }
   }
+  switch (p.tile) {
+    case T256x128w8: return launch_tile<T, 256, 128, 8, 4>(A, Bt, M, N, K, p, w, epi, s);
+    case T128x128w8: return launch_tile<T, 128, 128, 8, 4>(A, Bt, M, N, K, p, w, epi, s);
+    case T64x128w4: return launch_tile<T, 64, 128, 4, 2>(A, Bt, M, N, K, p, w, epi, s);
+  }
+  throw std::logic_error("GEMM plan without a tile kernel");
 }
 
 template <typename T, class Epi>
 void run_gemm(const T* A, const T* Bt, int M, int N, int K, const GemmWork& w, const Epi& epi,
               hipStream_t s) {
-  if (M <= 0) return;
-  const GemmPlan p = plan_gemm(M, N, K, sizeof(T) == 2);
-  if constexpr (sizeof(T) == 2) {
-    if (try_dma(A, Bt, M, N, K, p, w, epi, s)) return;
-  }
-  switch (p.tile) {
-    case T256x128w8: launch_tile<T, 256, 128, 8, 4, kTileKG[0]>(A, Bt, M, N, K, p, w, epi, s); break;
-    case T128x128w8: launch_tile<T, 128, 128, 8, 4, kTileKG[1]>(A, Bt, M, N, K, p, w, epi, s); break;
-    case T64x128w4: launch_tile<T, 64, 128, 4, 2, kTileKG[2]>(A, Bt, M, N, K, p, w, epi, s); break;
-    case T32x128w2: launch_tile<T, 32, 128, 2, 1, kTileKG[3]>(A, Bt, M, N, K, p, w, epi, s); break;
-    default: break;  // N % 128 != 0 is rejected at fv_create
-  }
+  if (M > 0) run_tile(A, Bt, M, N, K, plan_gemm(M, N, K, sizeof(T) == 2), w, epi, s);
 }
 
 }  // namespace
@@ -1163,9 +1108,8 @@ void run_gemm(const T* A, const T* Bt, int M, int N, int K, const GemmWork& w, c
 // Tile by row count: large M takes 256x256 tiles (fewer re-reads of A and
 // W) when that still gives about 200 blocks and no mostly idle second round,
 // else 128x128 (bf16; two workgroups per CU); medium M takes 128x128 tiles when that still gives
-// about 200 blocks (96 for an output or down projection), else 64x128;
-// small M takes 64- or 32-row tiles.  When a
-// grid has fewer than 128 tiles, k is split (KS a power of two, at least 4
+// about 200 blocks (96 for an output or down projection), else 64x128.
+// When a grid has fewer than 128 tiles, k is split (KS a power of two, at least 4
 // k-tiles per split, at most about 320 blocks) so that every CU streams its
 // share of the weights; with `reduce_fused` (the output and down
 // projections, whose split sum is fused into the next kernel at no extra
@@ -1194,9 +1138,9 @@ GemmPlan plan_tiles(int M, int N, int K, bool bf16, bool reduce_fused) {
   // slower at batch 44 (88) and 48 (120).  Two full rounds are best on
   // 256x256 tiles, also below 4096 rows (4000 rows, gate/up 83.6 -> 73.1 us).
   const long n256 = ntiles(T256x256big);
-  if (bf16 && K >= 1 << 22) {
-    p.tile = T32x128w2;  // the direct-to-LDS tiles' byte offsets (512 K) are 32-bit
-  } else if (bf16 && M >= 2048 && N % 256 == 0 && n256 >= 200 && !(n256 > 256 && n256 < 328)) {
+  // the direct-to-LDS kernel's byte offsets (512 K) are 32-bit
+  const bool dma = bf16 && K < 1 << 22;
+  if (dma && M >= 2048 && N % 256 == 0 && n256 >= 200 && !(n256 > 256 && n256 < 328)) {
     p.tile = T256x256big;
   } else if (M >= 4096) {
     p.tile = bf16 && N % 256 == 0 ? T128x128w8 : T256x128w8;
@@ -1217,11 +1161,10 @@ GemmPlan plan_tiles(int M, int N, int K, bool bf16, bool reduce_fused) {
                        !(bf16 && N > K && N <= 4096 && ntiles(T64x128w4) <= 512)
                    ? T128x128w8
                    : T64x128w4;
-  } else if (M > 32) {
-    p.tile = T64x128w4;
   } else {
-    p.tile = T32x128w2;
+    p.tile = T64x128w4;
   }
+  p.dma = dma && p.tile != T256x128w8;
   p.tiles = ntiles(p.tile);
   p.ks = 1;
   if ((p.tiles < 128 || (reduce_fused && p.tiles <= 160)) && p.tile != T256x256big)
@@ -1237,35 +1180,15 @@ GemmPlan plan_tiles(int M, int N, int K, bool bf16, bool reduce_fused) {
   return p;
 }
 
-
-// The direct-to-LDS tiles (every bf16 tile but 32x128) store bf16 partials.
-bool gemm_partials_bf16(const GemmPlan& p, bool bf16) {
-  return bf16 && p.ks > 1 &&
-         (p.tile == T256x256big || p.tile == T128x128w8 || p.tile == T64x128w4);
-}
-
 template <typename T>
 int gemm_partials(const T* A, const T* Bt, int M, int N, int K, const GemmWork& w,
                   hipStream_t s, bool* bf16_parts) {
   const GemmPlan p = plan_gemm(M, N, K, sizeof(T) == 2, true);
-  *bf16_parts = false;
-  if (p.tile == TFew) {
+  *bf16_parts = gemm_partials_bf16(p);
+  if (p.tile == TFew)
     few_partials(A, Bt, w.ws, M, N, K, p.ks, s);
-    return p.ks;
-  }
-  if (p.ks <= 1) return 1;
-  if constexpr (sizeof(T) == 2) {
-    if (try_dma(A, Bt, M, N, K, p, w, EpiNone{}, s)) {
-      *bf16_parts = true;
-      return p.ks;
-    }
-  }
-  switch (p.tile) {
-    case T256x128w8: launch_tile<T, 256, 128, 8, 4, kTileKG[0]>(A, Bt, M, N, K, p, w, EpiNone{}, s); break;
-    case T128x128w8: launch_tile<T, 128, 128, 8, 4, kTileKG[1]>(A, Bt, M, N, K, p, w, EpiNone{}, s); break;
-    case T64x128w4: launch_tile<T, 64, 128, 4, 2, kTileKG[2]>(A, Bt, M, N, K, p, w, EpiNone{}, s); break;
-    default: launch_tile<T, 32, 128, 2, 1, kTileKG[3]>(A, Bt, M, N, K, p, w, EpiNone{}, s);
-  }
+  else if (p.ks > 1)
+    run_tile(A, Bt, M, N, K, p, w, EpiNone{}, s);
   return p.ks;
 }
 

@@ -220,6 +220,7 @@ __device__ __forceinline__ float gelu_tanh_f(float x) {
 // K % 32 == 0 (fp32), 16-byte aligned base pointers.
 struct GemmPlan {
   int tile = -1, ks = 1, tiles = 0;  // tile shape id, split-K factor, output tiles
+  bool dma = false;                  // runs on the direct-to-LDS kernel (bf16)
   size_t ws_floats = 0;              // split-K workspace this GEMM needs
 };
 // reduce_fused: the plan of an output or down projection (its split sum
@@ -274,7 +275,7 @@ void gemm_gelu(const T* A, const T* Bt, T* out, int M, int N, int K, const GemmW
 // device before the first GEMM launch).
 hipError_t gemm_prepare();
 // Whether gemm_partials stores the partials of plan p as bf16.
-bool gemm_partials_bf16(const GemmPlan& p, bool bf16);
+inline bool gemm_partials_bf16(const GemmPlan& p) { return p.dma && p.ks > 1; }
 // Split-K GEMM that only writes its partials [KS][M][N] to w.ws; returns KS,
 // or 1 (nothing launched) when the plan does not split k.  *bf16_parts: the
 // partials are bf16 (the direct-to-LDS tiles), else fp32.

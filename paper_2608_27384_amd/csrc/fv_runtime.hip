@@ -378,7 +378,7 @@ void proj_norm_only(Handle* h, int K, int gate_off, int norm_off, int rowsT, hip
                     const void* pf, size_t pf_bytes) {
   const GemmPlan p = plan_gemm(rowsT, h->W, K, h->bf16, true);
   if (p.ks > 1)
-    launch_resid_norm<T>(h->gw.ws, gemm_partials_bf16(p, h->bf16), p.ks, h->hres, h->mod, h->Nmod,
+    launch_resid_norm<T>(h->gw.ws, gemm_partials_bf16(p), p.ks, h->hres, h->mod, h->Nmod,
                          gate_off, norm_off, h->C, h->cfg.rms_eps, (T*)h->u, rowsT, h->W,
                          pf, pf_bytes, s, h->film_per, few_rows(rowsT));
   else if (norm_off >= 0)
