@@ -1105,27 +1105,19 @@ void run_gemm(const T* A, const T* Bt, int M, int N, int K, const GemmWork& w, c
 
 }  // namespace
 
+namespace {
+
 // Tile by row count: large M takes 256x256 tiles (fewer re-reads of A and
 // W) when that still gives about 200 blocks and no mostly idle second round,
-// else 128x128 (bf16; two workgroups per CU); medium M takes 128x128 tiles when that still gives
-// about 200 blocks (96 for an output or down projection), else 64x128.
-// When a grid has fewer than 128 tiles, k is split (KS a power of two, at least 4
-// k-tiles per split, at most about 320 blocks) so that every CU streams its
-// share of the weights; with `reduce_fused` (the output and down
-// projections, whose split sum is fused into the next kernel at no extra
-// launch) grids of up to 160 tiles are split too.
-GemmPlan plan_gemm(int M, int N, int K, bool bf16, bool reduce_fused) {
-  if (N % 128 == 0 && M > 0 && few_rows(M)) {
-    GemmPlan p;
-    p.tile = TFew;
-    p.ks = reduce_fused ? few_splits(N, K, bf16 ? 2 : 4) : 1;
-    p.tiles = N / 16;
-    p.ws_floats = reduce_fused ? (size_t)p.ks * M * N : 0;
-    return p;
-  }
-  return plan_tiles(M, N, K, bf16, reduce_fused);
-}
-GemmPlan plan_tiles(int M, int N, int K, bool bf16, bool reduce_fused) {
+// else 128x128 (bf16; two workgroups per CU); medium M takes 128x128 tiles
+// when that still gives about 200 blocks (96 for an output or down
+// projection), else 64x128.  ks is the widest split: where a grid has fewer
+// than 128 tiles, a power of two with at least 4 k-tiles per split and at
+// most about 320 blocks, so that every CU streams its share of the weights;
+// with `reduce_fused` (the output and down projections, whose split sum is
+// fused into the next kernel at no extra launch) also for grids of up to 160
+// tiles.
+GemmPlan tile_plan(int M, int N, int K, bool bf16, bool reduce_fused) {
   GemmPlan p;
   if (N % 128 || M <= 0) return p;
   const int bk = bf16 ? 64 : 32, nk = K / bk;
@@ -1169,15 +1161,53 @@ GemmPlan plan_tiles(int M, int N, int K, bool bf16, bool reduce_fused) {
   p.ks = 1;
   if ((p.tiles < 128 || (reduce_fused && p.tiles <= 160)) && p.tile != T256x256big)
     while ((long)p.tiles * p.ks * 2 <= 320 && nk / (p.ks * 2) >= 4 && p.ks < 8) p.ks *= 2;
-  p.ws_floats = p.ks > 1 ? (size_t)p.ks * M * N : 0;
-  // Where the splits need a reduction kernel of their own (5-7 us), bf16
-  // splits under 32 k-tiles (0.45 us each) lose: QKV at 384 rows and 12
-  // k-tiles took 7.5 + 7.2 us split in two; 4 layers, 3 streams of 128
-  // tokens, 268 -> 252 us unsplit (fp32, 1.2 us a k-tile, keeps them: 416 us
-  // against 452).  The workspace still counts them, so that
-  // fv_decode_step_noalloc accepts the same steps.
-  if (bf16 && !reduce_fused && nk < 32) p.ks = 1;
   return p;
+}
+
+// Split of a bf16 product whose partials take a reduction kernel of their own:
+// the power of two up to `widest` that costs least, in us.  A k-tile takes
+// 0.30; a reduction 3.7 for two splits and 4.6 for more, 0.45 per MB of
+// partials, and 2 where the split grid passes one workgroup per CU (a launch,
+// unsplit / split in 4: gate/up of 384 columns at 80 rows and k 1920
+// 12.2 / 10.4, QKV of 512 columns at 80 rows and k 1792 13.6 / 12.5; of 2560
+// columns at 192 rows and k 1024 10.7 / 15.3).
+int cheapest_split(int M, int N, int nk, int tiles, int widest) {
+  const double mb = 4e-6 * M * N;
+  int best = 1;
+  double least = 0.30 * nk;
+  for (int ks = 2; ks <= widest; ks *= 2) {
+    const double t = 0.30 * nk / ks + (ks == 2 ? 3.7 : 4.6) + 0.45 * mb * ks +
+                     ((long)tiles * ks > 256 ? 2.0 : 0.0);
+    if (t < least) {
+      best = ks;
+      least = t;
+    }
+  }
+  return best;
+}
+
+}  // namespace
+
+GemmPlan plan_gemm(int M, int N, int K, bool bf16, bool reduce_fused) {
+  GemmPlan p;
+  if (N % 128 == 0 && M > 0 && few_rows(M)) {
+    p.tile = TFew;
+    p.ks = reduce_fused ? few_splits(N, K, bf16 ? 2 : 4) : 1;
+    p.tiles = N / 16;
+    p.ws_floats = reduce_fused ? (size_t)p.ks * M * N : 0;
+    return p;
+  }
+  p = tile_plan(M, N, K, bf16, reduce_fused);
+  // (fp32 k-tiles take 1.2 us: the widest split, 416 us against 452 without
+  // for 4 layers of width 512 at 400 rows)
+  if (bf16 && !reduce_fused) p.ks = cheapest_split(M, N, K / 64, p.tiles, p.ks);
+  p.ws_floats = p.ks > 1 ? (size_t)p.ks * M * N : 0;
+  return p;
+}
+
+size_t widest_split_floats(int M, int N, int K, bool bf16, bool reduce_fused) {
+  const GemmPlan p = tile_plan(M, N, K, bf16, reduce_fused);
+  return p.ks > 1 ? (size_t)p.ks * M * N : 0;
 }
 
 template <typename T>

@@ -226,8 +226,10 @@ struct GemmPlan {
 // reduce_fused: the plan of an output or down projection (its split sum
 // runs inside the next kernel, so splitting costs no launch).
 GemmPlan plan_gemm(int M, int N, int K, bool bf16, bool reduce_fused = false);
-// The tile kernels' plan alone (what plan_gemm gives above kFewRows rows).
-GemmPlan plan_tiles(int M, int N, int K, bool bf16, bool reduce_fused = false);
+// Split workspace of the product if every tile kernel split k as far as it
+// may: the bound by which fv_decode_step_noalloc admits a step (plan_gemm's
+// own ws_floats is never more, except a few-row product's).
+size_t widest_split_floats(int M, int N, int K, bool bf16, bool reduce_fused = false);
 
 // Split-K scratch shared by every GEMM of a handle (launches are stream
 // ordered): partial tiles, fp32, or bf16 for the direct-to-LDS kernel with

@@ -600,38 +600,46 @@ struct StepScratch {
   size_t part_o = 0, part_ml = 0, ws = 0;
   size_t total() const { return part_o + part_ml + ws; }
 };
-template <typename Plan>
-StepScratch scratch_of(const Handle* h, int B, int s, Plan plan) {
+// s: attention splits; floats(M, N, K, reduce_fused): a product's workspace.
+template <typename Floats>
+StepScratch scratch_of(const Handle* h, int B, int s, Floats floats) {
   StepScratch r;
   if (s > 1) {
     const size_t rows = (size_t)s * B * h->T * h->Hq;
     r.part_o = round256(rows * h->dh * h->esz);
     r.part_ml = round256(rows * 2 * 4);
   }
-  const int W = h->W, rk = B * h->K, rt = B * h->T, qd = h->Hq * h->dh;
-  const GemmPlan ps[] = {plan(rk, W, W, h->bf16, false),       plan(rk, h->Nmod, W, h->bf16, false),
-                         plan(rt, h->Nqkv, W, h->bf16, false), plan(rt, W, qd, h->bf16, true),
-                         plan(rt, h->Ngu, W, h->bf16, false),  plan(rt, W, h->F, h->bf16, true)};
-  for (const GemmPlan& p : ps) r.ws = std::max(r.ws, round256(p.ws_floats * 4));
+  const int W = h->W, rk = B * h->K, rt = B * h->T;
+  for (size_t f : {floats(rk, W, W, false), floats(rk, h->Nmod, W, false),
+                   floats(rt, h->Nqkv, W, false), floats(rt, W, h->Hq * h->dh, true),
+                   floats(rt, h->Ngu, W, false), floats(rt, W, h->F, true)})
+    r.ws = std::max(r.ws, round256(f * 4));
   return r;
 }
 // film: the step computes its FiLM maps (no schedule), which several streams
 // do in two products, of K and of (B - 1) K rows (enqueue_film_maps); fewer
 // rows may be split further than B K.
 StepScratch step_scratch(const Handle* h, int B, bool film) {
-  StepScratch r = scratch_of(h, B, attn_split(h, B), plan_gemm);
+  auto floats = [&](int M, int N, int K, bool fused) {
+    return plan_gemm(M, N, K, h->bf16, fused).ws_floats;
+  };
+  StepScratch r = scratch_of(h, B, attn_split(h, B), floats);
   if (film && B > 1)
     for (int rows : {h->K, (B - 1) * h->K})
       for (int N : {h->W, h->Nmod})
-        r.ws = std::max(r.ws, round256(plan_gemm(rows, N, h->W, h->bf16).ws_floats * 4));
+        r.ws = std::max(r.ws, round256(floats(rows, N, h->W, false) * 4));
   return r;
 }
-// What fv_decode_step_noalloc asks for: the step's scratch, and at least the
-// tile kernels' plan of it with 512 attention workgroups, so that the steps
-// it refuses do not depend on which kernels a row count takes.
+// What fv_decode_step_noalloc asks for: the step's scratch, and at least that
+// of the widest splits (attention towards 512 workgroups, the tile kernels'
+// products as far as they go), so that the steps it refuses do not depend on
+// the split and kernel that a size takes.
 size_t noalloc_bytes(const Handle* h, int B, bool film) {
+  auto floats = [&](int M, int N, int K, bool fused) {
+    return widest_split_floats(M, N, K, h->bf16, fused);
+  };
   return std::max(step_scratch(h, B, film).total(),
-                  scratch_of(h, B, attn_split_for(h, B, 512), plan_tiles).total());
+                  scratch_of(h, B, attn_split_for(h, B, 512), floats).total());
 }
 
 // Points the handle's split partials and split-K workspace at caller-given
