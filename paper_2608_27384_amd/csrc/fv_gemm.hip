@@ -1139,20 +1139,22 @@ GemmPlan tile_plan(int M, int N, int K, bool bf16, bool reduce_fused) {
   } else if (M > 256) {
     // (an output or down projection takes 128x128 tiles from 96 of them on:
     // with k split in two they beat 64x128 tiles, batch 3 2790 -> 2722 us)
-    if (reduce_fused && bf16 && ntiles(T128x128w8) >= 96)
+    // 128x128 from 200 tiles on, except narrow products whose 64x128 tiles fit
+    // one round of two workgroups per CU where the 128x128 tiles hardly fill
+    // theirs or just pass it (4-layer passes, 128x128 / 64x128: QKV at 1155
+    // rows, 200 tiles, 514 / 502 us; a plain MLP's up product at 1300 rows,
+    // 264 tiles, 352 / 342).  In between the larger tiles read less: QKV at
+    // 1300 rows, 220 tiles, 507 / 520; 4096 columns of gate/up at 1000 rows,
+    // 256 tiles, 291 / 295.  N > K leaves out the projections back to the
+    // width (8 streams of 500 tokens: 1020 us on 128x128 tiles, 1067 on
+    // 64x128).
+    const int t128 = ntiles(T128x128w8);
+    const bool narrow = bf16 && N > K && N <= 4096 && ntiles(T64x128w4) <= 512 &&
+                        (t128 <= 208 || t128 > 256);
+    if (reduce_fused && bf16 && t128 >= 96)
       p.tile = T128x128w8;
     else
-      // 128x128 from 200 tiles on, except narrow products whose 64x128 tiles
-      // fit one round of two workgroups per CU, so that one's long epilogue
-      // runs over the other's main loop (QKV at 1155 rows, 200 and 380 tiles:
-      // 4-layer pass 566 -> 552 us; gate/up at 500 rows, 256 and 512 tiles,
-      // is faster on 128x128: 13.8 us against 17.3).  N > K leaves out the
-      // projections back to the width (8 streams of 500 tokens: 1020 us on
-      // 128x128 tiles, 1067 on 64x128)
-      p.tile = ntiles(T128x128w8) >= 200 &&
-                       !(bf16 && N > K && N <= 4096 && ntiles(T64x128w4) <= 512)
-                   ? T128x128w8
-                   : T64x128w4;
+      p.tile = t128 >= 200 && !narrow ? T128x128w8 : T64x128w4;
   } else {
     p.tile = T64x128w4;
   }

@@ -1,4 +1,4 @@
-"""Split rule of the GEMM plan, on the host: each row is a size at
+"""Tile and split rules of the GEMM plan, on the host: each row is a size at
 which both sides were timed, and the side that was faster (a split's reduction
 counted).  The plan functions are C++ symbols of the library; calling them
 needs no GPU."""
@@ -30,6 +30,15 @@ def test_split_where_it_was_faster(M, N, K, split):
     p = _plan(M, N, K)
     assert (p.ks > 1) == split
     assert p.ws_floats == (p.ks * M * N if split else 0)
+
+
+# (rows, columns, k, tiles of the faster tile: 64x128 or 128x128)
+@pytest.mark.parametrize("M,N,K,tiles", [
+    (1155, 2560, 1024, 19 * 20), (1300, 3072, 1024, 21 * 24), (1300, 3072, 768, 21 * 24),
+    (1300, 2560, 1024, 11 * 20), (1500, 2560, 1536, 12 * 20), (850, 4096, 1024, 7 * 32),
+    (1000, 4096, 1024, 8 * 32), (1150, 3072, 768, 9 * 24)])
+def test_tile_that_was_faster(M, N, K, tiles):
+    assert _plan(M, N, K).tiles == tiles
 
 
 def test_long_products_leave_the_direct_to_lds_kernel():
