@@ -10,6 +10,7 @@
 #include <vector>
 
 #include "fv_internal.h"
+#include "fv_pack.h"
 
 struct fv_handle_s : public fv::Handle {};
 
@@ -93,26 +94,17 @@ void* dalloc(Handle* h, size_t bytes) {
   return p;
 }
 
-// Uploads a weight, host fp32 [rows][K] (rows a multiple of 16), as the
-// handle's storage type (bf16 RNE or fp32) in the tiled layout of tile_off.
-template <typename T, typename Conv>
-void* upload_tiled(Handle* h, const std::vector<float>& v, int K, Conv conv) {
-  constexpr int E = 16 / (int)sizeof(T);
-  std::vector<T> b(v.size());
-  const int rows = (int)(v.size() / K);
-  for (int r = 0; r < rows; ++r)
-    for (int k = 0; k < K; k += E) {
-      const float* src = v.data() + (size_t)r * K + k;
-      T* dst = b.data() + tile_off<T>(r, k, K);
-      for (int e = 0; e < E; ++e) dst[e] = conv(src[e]);
-    }
-  void* d = dalloc(h, b.size() * sizeof(T));
-  FV_HIP(hipMemcpy(d, b.data(), b.size() * sizeof(T), hipMemcpyHostToDevice));
+// Uploads host fp32 values as the handle's storage type (bf16 RNE or fp32).
+void* upload_T(Handle* h, const TiledRows& v) {
+  void* d = dalloc(h, v.size() * h->esz);
+  if (h->bf16) {
+    std::vector<uint16_t> b(v.size());
+    for (size_t i = 0; i < v.size(); ++i) b[i] = host_bf16(v.data()[i]);
+    FV_HIP(hipMemcpy(d, b.data(), b.size() * 2, hipMemcpyHostToDevice));
+  } else {
+    FV_HIP(hipMemcpy(d, v.data(), v.size() * 4, hipMemcpyHostToDevice));
+  }
   return d;
-}
-void* upload_T(Handle* h, const std::vector<float>& v, int K) {
-  if (h->bf16) return upload_tiled<uint16_t>(h, v, K, host_bf16);
-  return upload_tiled<float>(h, v, K, [](float x) { return x; });
 }
 
 // fp32 upload; in bf16 mode values are first rounded to bf16 (stored as fp32).
@@ -130,11 +122,6 @@ float* upload_f32(Handle* h, const float* src, size_t n, bool round) {
 
 void need(const void* p, const char* what) {
   if (!p) fail(FV_ERR_INVALID_ARG, std::string("NULL pointer: ") + what);
-}
-
-// Appends rows of Bt [out][in] for output columns [c0, c0+cnt) of W [in][out].
-void append_out_major(std::vector<float>& dst, const float* W, int in, int out, int col) {
-  for (int k = 0; k < in; ++k) dst.push_back(W[(size_t)k * out + col]);
 }
 
 void validate_cfg(const fv_cfg& c) {
@@ -813,78 +800,59 @@ fv_status fv_create(const fv_weights* w, const fv_cfg* cfg, fv_handle* out) {
     H.w_out = upload_f32(h, w->w_out, (size_t)W * H.A, true);
     H.b_out = upload_f32(h, w->b_out, H.A, true);
     if (H.A <= 32) {
-      auto rounded = [&](float x) {
-        if (!H.bf16) return x;
-        const uint32_t u = (uint32_t)host_bf16(x) << 16;
-        std::memcpy(&x, &u, 4);
-        return x;
-      };
-      std::vector<float> in_t((size_t)W * 32), out_t((size_t)32 * W);
-      for (int c = 0; c < W; ++c)
-        for (int a = 0; a < H.A; ++a) {
-          in_t[(size_t)c * 32 + a] = w->w_in[(size_t)a * W + c];
-          out_t[(size_t)a * W + c] = w->w_out[(size_t)c * H.A + a];
-        }
-      H.w_in_t = static_cast<float*>(upload_tiled<float>(h, in_t, 32, rounded));
-      H.w_out_t = static_cast<float*>(upload_tiled<float>(h, out_t, W, rounded));
+      TiledRows in_t(W, 32, 4), out_t(32, W, 4);
+      for (int c = 0; c < W; c += 16) in_t.append16(w->w_in, W, c, H.A);
+      for (int a = 0; a < 32; a += 16) out_t.append16(w->w_out, H.A, a, W);
+      H.w_in_t = upload_f32(h, in_t.data(), in_t.size(), true);
+      H.w_out_t = upload_f32(h, out_t.data(), out_t.size(), true);
     }
+    const int E = 16 / H.esz;  // elements of a 16-byte piece
+    auto upload_linear = [&](const float* Wm, int in, int out) {
+      TiledRows v(out, in, E);
+      v.append(Wm, out, 0, out);
+      return upload_T(h, v);
+    };
+    H.w_t1 = upload_linear(w->w_t1, W, W);
+    H.w_t2 = upload_linear(w->w_t2, W, W);
     {
-      std::vector<float> v;
-      v.reserve((size_t)W * W);
-      for (int c = 0; c < W; ++c) append_out_major(v, w->w_t1, W, W, c);
-      H.w_t1 = upload_T(h, v, W);
-      v.clear();
-      for (int c = 0; c < W; ++c) append_out_major(v, w->w_t2, W, W, c);
-      H.w_t2 = upload_T(h, v, W);
-    }
-    {
-      std::vector<float> v, bias;
-      v.reserve((size_t)H.Nmod * W);
+      TiledRows v(H.Nmod, W, E);
+      std::vector<float> bias;
       for (int n = 0; n <= 2 * L; ++n) {
         const int cols = n < 2 * L ? 3 * W : 2 * W;  // the final norm's gate is never used
-        for (int c = 0; c < cols; ++c) {
-          append_out_major(v, w->w_mod[n], W, 3 * W, c);
-          bias.push_back(w->b_mod[n][c]);
-        }
+        v.append(w->w_mod[n], 3 * W, 0, cols);
+        bias.insert(bias.end(), w->b_mod[n], w->b_mod[n] + cols);
       }
-      H.w_mod = upload_T(h, v, W);
+      H.w_mod = upload_T(h, v);
       H.b_mod = upload_f32(h, bias.data(), bias.size(), true);
     }
     const int qd = H.Hq * dh, kd = H.Hkv * dh;
     for (int l = 0; l < L; ++l) {
-      std::vector<float> v;
-      v.reserve((size_t)H.Nqkv * W);
+      TiledRows qkv(H.Nqkv, W, E);
       // queries and keys: per head, rotary partners (d, d + dh/2) packed into
       // columns 64p + i and 64p + 32 + i, d = 32p + i
       auto rot_head = [&](const float* Wm, int out, int head) {
-        for (int pc = 0; pc < dh; ++pc) {
-          const int p = pc >> 6, i = pc & 63;
-          const int d = i < 32 ? 32 * p + i : dh / 2 + 32 * p + (i - 32);
-          append_out_major(v, Wm, W, out, head * dh + d);
+        for (int p = 0; p < dh / 64; ++p) {
+          qkv.append(Wm, out, head * dh + 32 * p, 32);
+          qkv.append(Wm, out, head * dh + dh / 2 + 32 * p, 32);
         }
       };
       for (int hq = 0; hq < H.Hq; ++hq) rot_head(w->wq[l], qd, hq);
       for (int g = 0; g < H.Hkv; ++g) rot_head(w->wk[l], kd, g);
-      for (int c = 0; c < kd; ++c) append_out_major(v, w->wv[l], W, kd, c);
-      H.wqkv.push_back(upload_T(h, v, W));
-      v.clear();
-      for (int c = 0; c < W; ++c) append_out_major(v, w->wo[l], qd, W, c);
-      H.wo.push_back(upload_T(h, v, qd));
-      v.clear();
+      qkv.append(w->wv[l], kd, 0, kd);
+      H.wqkv.push_back(upload_T(h, qkv));
+      H.wo.push_back(upload_linear(w->wo[l], qd, W));
       if (cfg->mlp_gated) {
         // gate/up partners packed into columns 64p + i and 64p + 32 + i, f = 32p + i
-        for (int pc = 0; pc < 2 * F; ++pc) {
-          const int p = pc >> 6, i = pc & 63;
-          if (i < 32) append_out_major(v, w->wg[l], W, F, 32 * p + i);
-          else append_out_major(v, w->wu[l], W, F, 32 * p + i - 32);
+        TiledRows gu(H.Ngu, W, E);
+        for (int f = 0; f < F; f += 32) {
+          gu.append(w->wg[l], F, f, 32);
+          gu.append(w->wu[l], F, f, 32);
         }
+        H.wgu.push_back(upload_T(h, gu));
       } else {
-        for (int c = 0; c < F; ++c) append_out_major(v, w->wu[l], W, F, c);
+        H.wgu.push_back(upload_linear(w->wu[l], W, F));
       }
-      H.wgu.push_back(upload_T(h, v, W));
-      v.clear();
-      for (int c = 0; c < W; ++c) append_out_major(v, w->wd[l], F, W, c);
-      H.wd.push_back(upload_T(h, v, F));
+      H.wd.push_back(upload_linear(w->wd[l], F, W));
     }
 
     // ---- rotary tables, built in fp64 and rounded to fp32
