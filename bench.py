@@ -101,6 +101,9 @@ DEBUG_STAGES = {"film_maps": 0, "qkv_gemm": 1, "gate_up_gemm": 3, "attention": 4
                 "down_proj_norm": 11}
 
 
+FEW_ROWS = 64  # token (or FiLM) rows up to which a product takes the one-pass kernel
+
+
 def film_rows(w):
     """FiLM-map rows a step computes: with several streams whose noise levels
     are the same staircase (these inputs), stream 0's K rows serve them all."""
@@ -111,43 +114,51 @@ def stage_kernels(w, split_k: int, n_split: int):
     """Stage -> (kernel label, substring of the kernel's name in a rocprofv3
     trace).  Stages that launch the same kernel share a label."""
     bf16 = w.dtype == synth.BF16
-    rows_k, rows_t = w.batch * w.n_chunks, w.batch * w.tokens
-    rows_f = film_rows(w)
-    if bf16:
-        attn = ("attn16d_kernel" if w.head_dim in (128, 256) else "attn16_kernel")
+    rows_t, rows_f = w.batch * w.tokens, film_rows(w)
+    W, A = w.width, w.action_dim
+    few = rows_t <= FEW_ROWS
+
+    def gemm(rows, epi, what):
+        if rows <= FEW_ROWS:
+            return (f"few_gemm_kernel<..., Few{epi}> ({what})", f"Few{epi}")
+        kern = "gemm_dma_kernel" if bf16 else "gemm_kernel"
+        return (f"{kern}<..., Epi{epi}> ({what})", f"Epi{epi}")
+
+    attn = ("attn_few_kernel" if few else "attn_kernel" if not bf16 else
+            "attn16d_kernel" if w.head_dim in (128, 256) else "attn16_kernel")
+    what = "output and down projections"
+    if few:
+        proj = gemm(rows_t, "Partial", f"k-slice partials, {what}")
+    elif split_k > 1:
+        proj = gemm(rows_t, "None", f"split-K partials, {what}")
     else:
-        attn = "attn_kernel"
-    proj = (("gemm_dma_kernel<..., EpiNone> (split-K partials, output and down projections)",
-             "EpiNone") if split_k > 1 else
-            ("gemm_dma_kernel<..., EpiGatedResid> (output and down projections)",
-             "EpiGatedResid"))
+        proj = gemm(rows_t, "GatedResid", what)
     norm = (("resid_norm_kernel (split-K sum + gated residual + FiLM norm)", "resid_norm_kernel")
             if split_k > 1 else ("adarms_kernel (FiLM norm)", "adarms_kernel"))
-    mlp = (("gemv_bias_silu_kernel (time-MLP)", "gemv_bias_silu_kernel") if rows_f <= 16 else
-           ("gemm<..., EpiBiasSilu> (time-MLP)", "EpiBiasSilu"))
-    many = rows_t >= 4096 and w.width <= 1024
-    small_head = not many and w.width <= 1024 and w.action_dim <= 32 and w.action_dim % 4 == 0
-    stream_film = bf16 and rows_f <= 16 and w.width in (512, 1024)
+    mlp = gemm(rows_f, "BiasSilu", "time-MLP")
+    many, small = rows_t >= 1024 and W <= 1024, W <= 1024
+    fusable = small and W % 128 == 0 and A <= 32 and A % 4 == 0
+    embed = ("embed_adarms_mma_kernel" if many and A <= 32 else
+             "embed_adarms_small_kernel" if small and A <= 32 else "embed_adarms_kernel")
+    head = ("final_mma_kernel" if many and fusable else
+            "final_small_kernel" if fusable else "final_kernel")
     out = {
         "time_embed": ("time_embed_kernel (fp64 sinusoidal embedding)", "time_embed_kernel"),
         "time_mlp1": mlp, "time_mlp2": mlp,
         "film_maps": (("stream_bias_f32_kernel (all FiLM maps, weights streamed)",
-                       "stream_bias_f32_kernel") if stream_film else
-                      ("gemm<..., EpiBiasF32> (all FiLM maps)", "EpiBiasF32")),
-        "embed": ((embed := ("embed_adarms_rows_kernel" if many else
-                             "embed_adarms_small_kernel" if small_head else
-                             "embed_adarms_kernel")) + " (in-projection + first FiLM norm)", embed),
-        "qkv_gemm": ("gemm_dma_kernel<..., EpiQkv> (QKV + rotary + arena)", "EpiQkv"),
+                       "stream_bias_f32_kernel")
+                      if bf16 and rows_f <= 16 and W in (512, 1024) else
+                      gemm(rows_f, "BiasF32", "all FiLM maps")),
+        "embed": (embed + " (in-projection + first FiLM norm)", embed),
+        "qkv_gemm": gemm(rows_t, "Qkv", "QKV + rotary + arena"),
         "attention": (f"{attn} (chunk-causal + prefix attention)", attn),
         "o_proj_gemm": proj, "down_proj_gemm": proj,
         "o_proj_norm": norm, "down_proj_norm": norm,
-        "gate_up_gemm": ("gemm_dma_kernel<..., EpiGeglu> (gate/up + GeGLU)",
-                         "EpiGeglu" if w.mlp_gated else "EpiGelu"),
-        "head": ((head := ("final_rows_kernel" if many else
-                           "final_small_kernel" if small_head else "final_kernel")) +
-                 " (final FiLM norm + velocity head)", head),
-        "euler_shift": (("final_small_kernel<true> (Euler + emit + shift + refill fused into "
-                         "the velocity head)", "final_small_kernel<true>") if small_head else
+        "gate_up_gemm": (gemm(rows_t, "Geglu", "gate/up + GeGLU") if w.mlp_gated else
+                         gemm(rows_t, "Gelu", "up + GELU")),
+        "head": (head + " (final FiLM norm + velocity head)", head),
+        "euler_shift": ((f"{head}<true> (Euler + emit + shift + refill fused into the velocity "
+                         "head)", f"{head}<true>") if fusable else
                         ("euler_shift_kernel (Euler + emit + shift + refill)",
                          "euler_shift_kernel")),
     }
@@ -179,7 +190,8 @@ def stage_work(w, lens, n_split: int, split_k: int):
     h_rw = 2 * rows_t * W * 4                       # fp32 residual read + write
     if split_k > 1:
         proj_out = rows_t * W * e                   # the product once, element type
-        norm_bytes = split_k * rows_t * W * (2 if e == 2 else 4) + h_rw + rows_t * W * e
+        part = 2 if e == 2 and rows_t > FEW_ROWS else 4
+        norm_bytes = split_k * rows_t * W * part + h_rw + rows_t * W * e
     else:
         proj_out = h_rw                             # gated residual in the epilogue
         norm_bytes = rows_t * W * 4 + rows_t * W * e
