@@ -49,17 +49,20 @@ SIMD_NUM = 1024                 # 256 CUs x 4 SIMDs
 XCD_NUM = 8                     # GRBM_GUI_ACTIVE arrives summed over the 8 dies
 
 GEMM_SRC = ("csrc/fv_gemm.hip", "csrc/fv_internal.h")
+FEW_SRC = ("csrc/fv_few.hip", "csrc/fv_internal.h")
 ATTN_SRC = ("csrc/fv_attn.hip", "csrc/fv_internal.h")
 MISC_SRC = ("csrc/fv_misc.hip", "csrc/fv_internal.h")
-ALL_SRC = ("csrc/fv_gemm.hip", "csrc/fv_attn.hip", "csrc/fv_misc.hip", "csrc/fv_runtime.hip",
-           "csrc/fv_internal.h")
+ALL_SRC = ("csrc/fv_gemm.hip", "csrc/fv_few.hip", "csrc/fv_attn.hip", "csrc/fv_misc.hip",
+           "csrc/fv_runtime.hip", "csrc/fv_internal.h")
 
 # kernel key (substring of its name in a trace) -> source files that define it
 KERNELS: Dict[str, Tuple[str, ...]] = {
     "EpiBiasF32": GEMM_SRC, "EpiQkv": GEMM_SRC, "EpiGeglu": GEMM_SRC, "EpiGelu": GEMM_SRC,
-    "EpiNone": GEMM_SRC, "EpiGatedResid": GEMM_SRC,
+    "EpiNone": GEMM_SRC, "EpiGatedResid": GEMM_SRC, "stream_bias_f32_kernel": GEMM_SRC,
+    "FewBiasF32": FEW_SRC, "FewQkv": FEW_SRC, "FewGeglu": FEW_SRC, "FewGelu": FEW_SRC,
+    "FewPartial": FEW_SRC,
     "attn16d_kernel": ATTN_SRC, "attn16_kernel": ATTN_SRC, "attn_kernel": ATTN_SRC,
-    "attn_combine": ATTN_SRC,
+    "attn_few_kernel": ATTN_SRC, "attn_combine": ATTN_SRC,
     "resid_norm_kernel": MISC_SRC, "adarms_kernel": MISC_SRC,
 }
 
@@ -171,7 +174,8 @@ def bytes_summary(fetch_csv, write_csv, kernel, workload, launches, cmds) -> str
 def _step_end(name: str) -> bool:
     """A decode step ends with its Euler update: the Euler kernel, or the
     velocity head with the update fused in."""
-    return "euler_shift_kernel" in name or "final_small_kernel<true>" in name
+    return any(k in name for k in ("euler_shift_kernel", "final_small_kernel<true>",
+                                   "final_mma_kernel<true>"))
 
 
 def _step_window(ds) -> Tuple[int, int, int]:

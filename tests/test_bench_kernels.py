@@ -1,12 +1,13 @@
-"""The benchmark's stage-to-kernel map names kernels that the library has, by
-the library's own rules (at most 64 rows, 1024 rows and more, the fused Euler
-update)."""
+"""The benchmark's stage-to-kernel map and the counter summaries name kernels
+that the library has, by the library's own rules (at most 64 rows, 1024 rows
+and more, the fused Euler update)."""
 import subprocess
 
 import pytest
 
 import bench
 import synth
+from paper_2608_27384_amd import counters
 from paper_2608_27384_amd.flashvla import LIB_PATH
 
 
@@ -43,3 +44,19 @@ def test_kernels_by_the_rows_of_a_pass():
     b64 = bench.stage_kernels(synth.workload("batched64"), 1, 1)
     assert [b64[s][1] for s in ("o_proj_gemm", "embed", "head", "euler_shift")] == [
         "EpiGatedResid", "embed_adarms_mma_kernel", "final_mma_kernel", "final_mma_kernel<true>"]
+
+
+@pytest.mark.parametrize("w", _workloads(), ids=lambda w: w.name)
+def test_a_step_ends_at_its_euler_update(w):
+    """The counter summaries cut a trace into steps there."""
+    stages = bench.stage_kernels(w, 4, 4)
+    ends = [s for s, (_, match) in stages.items() if counters._step_end(match)]
+    assert ends == ["euler_shift"]
+
+
+def test_a_change_of_any_kernel_source_makes_the_summaries_stale():
+    import glob
+    import os
+    src = {"csrc/" + os.path.basename(p)
+           for p in glob.glob(os.path.join(counters.PKG, "csrc", "*.hip"))}
+    assert src <= set(counters.ALL_SRC)
