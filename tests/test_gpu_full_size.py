@@ -84,10 +84,10 @@ def test_velocity_parity_batched64_all_streams():
 def test_velocity_parity_ragged_large_m():
     """9 streams of the batched workload: 4500 token rows, so the large-row
     GEMM tiles (256 rows) end in a partial tile of 148 rows, which belongs to
-    the last stream.  Then one decode step, which at this many rows runs the
-    velocity head and the queue update as separate kernels: buffer and emitted
-    chunk bit for bit against the fp32 queue update of the GPU's own velocity,
-    refill against the oracle's Philox draw."""
+    the last stream.  Then one decode step, with the queue update fused into
+    the velocity head on the matrix units: buffer and emitted chunk bit for
+    bit against the fp32 queue update of the GPU's own velocity, refill
+    against the oracle's Philox draw."""
     w = synth.workload("batched64").replace(name="batched9", batch=9)
     case = Case(w)
     try:

@@ -2,12 +2,14 @@
 embedding and velocity head on the matrix units (from 1024 rows on, partly
 filled 16-row tiles, action dims that are no multiple of 4), QKV on 64x128
 tiles in one round (1300 rows), gate/up on 256x256 tiles from 2048 rows on.
-The step's fused Euler update equals the host's on the same velocities bit for
-bit.  Tolerances are the suite's: 1e-2 of the largest value for bf16 operands,
+The step's Euler update, fused into the head or (an action dim that is no
+multiple of 4) the queue update kernel, equals the host's on the same velocities
+bit for bit, and its refill the oracle's Philox draw.  Tolerances are the suite's: 1e-2 of the largest value for bf16 operands,
 1e-4 for fp32."""
 import numpy as np
 import pytest
 
+import oracle
 import synth
 from gpu_util import Case, host, rel_err, tol
 
@@ -43,5 +45,8 @@ def test_many_rows(shape):
         x = case.x.astype(np.float32) - dt[:, :, None, None] * v
         assert np.array_equal(out, x[:, 0])
         assert np.array_equal(new[:, :-1], x[:, 1:])
+        z = np.stack([oracle.gaussian_chunk(case.noise_seed + b, 0, C, A) for b in range(B)])
+        assert np.max(np.abs(new[:, -1] - z)) <= 1e-6
+        assert np.count_nonzero(new[:, -1] != z) <= 2  # fp64 libm ties only
     finally:
         case.close()

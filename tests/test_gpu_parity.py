@@ -265,8 +265,9 @@ def test_bookkeeping_bit_exact(name):
 @pytest.mark.parametrize("name,K,C", [("tiny_fp32", 4, 8), ("small_bf16_b3", 3, 10),
                                       ("tiny_fp32", 256, 2), ("small_fp32_b2", 255, 1)])
 def test_euler_shift_entry_point_bit_exact(name, K, C):
-    """fv_euler_shift, the separate queue-update kernel that the many-row
-    decode step also runs, on a caller-given velocity: the buffer and emitted
+    """fv_euler_shift, the separate queue-update kernel that a decode step also
+    runs where the velocity head cannot take the update, on a caller-given
+    velocity: the buffer and emitted
     chunk equal, bit for bit, the fp32 queue update; the refill equals the
     oracle's Philox draw; a stream still in cold start pops padding and emits
     zeros; the valid-slot counts and the step counter advance.  Buffer
@@ -305,8 +306,8 @@ def test_euler_shift_entry_point_bit_exact(name, K, C):
 def test_fp32_many_rows():
     """fp32 mode at 4800 token rows (24 streams of 10 chunks x 20 tokens,
     ragged prefixes): the large-row fp32 GEMM tiles (256 x 128, the last one
-    partial), the many-row head and the separate queue update.  Velocities of
-    three streams against the oracle within 1e-4; one decode step, buffer and
+    partial), the head on the matrix units with the queue update fused in.
+    Velocities of three streams against the oracle within 1e-4; one decode step, buffer and
     emitted chunks bit for bit against the fp32 queue update of the GPU's own
     velocity for every stream."""
     w = synth.workload("small_fp32_b2").replace(name="fp32_rows", n_chunks=10, chunk_len=20,
