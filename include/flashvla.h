@@ -205,11 +205,15 @@ fv_status fv_decode_step(fv_handle h, float *buffer, const float *t_per_chunk, f
  * key-split partials and the split-K partial tiles -- lives in a static
  * device array of FV_NOALLOC_SCRATCH_BYTES (24 MiB) that each GPU the library
  * runs on holds until the process ends, instead of the handle's own scratch.
- * A step that needs more (fv_query FV_QUERY_NOALLOC_SCRATCH_BYTES; the
- * pi0.5-shaped expert needs about 21 MB at batch 1 and more at batch 2 to 8)
- * returns FV_ERR_INVALID_ARG.  Every call on a GPU shares that GPU's array
- * and nothing in it needs to start at zero; calls that overlap on one GPU
- * (from any handle or stream) race.
+ * A step is admitted by a bound on its scratch that is never less than what it
+ * uses: that of the widest splits its sizes allow (attention towards 512
+ * workgroups, every product as far as its kernel may), so that the steps
+ * refused do not change with the splits and kernels a size takes.  One whose
+ * bound exceeds the array (fv_query FV_QUERY_NOALLOC_SCRATCH_BYTES; the
+ * pi0.5-shaped expert is at 24.8 MB, 23.7 MiB, at batch 1 and above the array
+ * at batch 2 to 15) returns FV_ERR_INVALID_ARG.  Every call on a GPU shares
+ * that GPU's array and nothing in it needs to start at zero; calls that
+ * overlap on one GPU (from any handle or stream) race.
  * Errors: as fv_decode_step, plus FV_ERR_INVALID_ARG (scratch too small for
  * the active batch) and FV_ERR_HIP (the array's address is unavailable).
  */
@@ -345,10 +349,10 @@ fv_status fv_set_graph_mode(fv_handle h, int32_t enabled);
  *    query tile into at batch `batch` (1: no split, no combine kernel);
  *  FV_QUERY_DEVICE_BYTES: device memory the handle holds (weights, prefix
  *    arenas, scratch, workspace), in bytes; `batch` is ignored;
- *  FV_QUERY_NOALLOC_SCRATCH_BYTES: static scratch fv_decode_step_noalloc
- *    asks for at batch `batch` when it is given t (a step is accepted when
- *    this is at most FV_NOALLOC_SCRATCH_BYTES; one with the installed
- *    schedule computes no FiLM maps and may ask for less);
+ *  FV_QUERY_NOALLOC_SCRATCH_BYTES: the bound by which fv_decode_step_noalloc
+ *    admits a step at batch `batch` that is given t (accepted when at most
+ *    FV_NOALLOC_SCRATCH_BYTES; a step with the installed schedule computes no
+ *    FiLM maps and may have a lower one);
  *  FV_QUERY_OUT_PROJ_SPLITS: split-K factor of the output projection at batch
  *    `batch` (1: unsplit, the gated residual runs in the GEMM's epilogue;
  *    more: split partials reduced with the residual and the next norm).

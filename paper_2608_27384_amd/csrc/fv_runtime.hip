@@ -1095,8 +1095,8 @@ fv_status fv_decode_step_noalloc(fv_handle h, float* buffer, const float* t, flo
     const StepScratch need = step_scratch(h, B, t != nullptr);
     const size_t asked = noalloc_bytes(h, B, t != nullptr);
     if (asked > kStaticScratchBytes)
-      fail(FV_ERR_INVALID_ARG, "a step at batch " + std::to_string(B) + " needs " +
-                                   std::to_string(asked) +
+      fail(FV_ERR_INVALID_ARG, "the widest splits of a step at batch " + std::to_string(B) +
+                                   " take " + std::to_string(asked) +
                                    " bytes of scratch; the static scratch holds " +
                                    std::to_string(kStaticScratchBytes) +
                                    " (use fv_decode_step)");
