@@ -16,6 +16,8 @@
 // consecutive rows, 16 per wave (bf16: 8 waves, 128 rows; fp32: 4 waves, 64
 // rows, RG groups of 16 rows per wave sharing every K and V fragment read
 // from LDS), so rows of all heads that share the kv head reuse one K/V tile.
+// A pass of at most kFewRows rows takes 16 rows per block instead, which no
+// K/V tile is shared for (attn_few_kernel).
 // For bf16 head dims 128 and 256 (attn16d_kernel) the K/V tiles go from
 // memory straight into a ring of LDS stages, three tiles ahead; otherwise the
 // next K/V tile is loaded into registers while the current one is
@@ -86,21 +88,20 @@ __device__ __forceinline__ KeyTiles key_tiles(int P, int C, int K, int first, in
   return r;
 }
 
-template <typename T, int DH, int KT, int RG>
+// The fp32 kernel of passes above kFewRows rows.
+template <int DH, int KT, int RG>
 __global__ __launch_bounds__(256) void attn_kernel(AttnArgs a) {
+  using T = float;
   constexpr int kRowsPerWave = 16 * RG;
   constexpr int kRowsPerBlock = 4 * kRowsPerWave;
-  using MF = Mfma<T>;
   constexpr int EPV = 16 / (int)sizeof(T);
   constexpr int LDK = DH + EPV;
   constexpr int LDV = KT + EPV;
   constexpr int NST = KT / 16;
-  constexpr int NKS = DH / MF::KM;
+  constexpr int NKS = DH / 4;
   constexpr int NDT = DH / 16;
   constexpr int VK = KT * DH / EPV, VV = DH * KT / EPV;  // 16-byte vectors per tile
   constexpr int NVK = (VK + 255) / 256, NVV = (VV + 255) / 256;
-  constexpr bool kBF16 = sizeof(T) == 2;
-  static_assert(!kBF16 || NST % 2 == 0, "bf16 path pairs 16-key subtiles");
 
   __shared__ __attribute__((aligned(16))) T sK[KT * LDK];
   __shared__ __attribute__((aligned(16))) T sV[DH * LDV];
@@ -136,13 +137,13 @@ __global__ __launch_bounds__(256) void attn_kernel(AttnArgs a) {
   const KeyTiles kts = key_tiles(P, C, K, first, a.mask_mode, tile0 / G, rlast / G, KT);
   const int kt_begin = (split * kts.n) / a.n_split, kt_end = ((split + 1) * kts.n) / a.n_split;
 
-  typename MF::frag qf[RG][NKS];
+  float qf[RG][NKS];
 #pragma unroll
   for (int q = 0; q < RG; ++q) {
     const T* qrow = reinterpret_cast<const T*>(a.q) +
                     ((size_t)(b * a.tokens + tok[q]) * a.n_q_heads + head[q]) * DH;
 #pragma unroll
-    for (int ks = 0; ks < NKS; ++ks) qf[q][ks] = MF::load(qrow + ks * MF::KM + MF::KG * lg);
+    for (int ks = 0; ks < NKS; ++ks) qf[q][ks] = qrow[4 * ks + lg];
   }
 
   f32x4 acc[RG][NDT];
@@ -219,10 +220,10 @@ __global__ __launch_bounds__(256) void attn_kernel(AttnArgs a) {
       for (int q = 0; q < RG; ++q) s[q][st] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int ks = 0; ks < NKS; ++ks) {
-        const typename MF::frag kf =
-            MF::load(&sK[(16 * st + l16) * LDK + ks * MF::KM + MF::KG * lg]);
+        const float kf = sK[(16 * st + l16) * LDK + 4 * ks + lg];
 #pragma unroll
-        for (int q = 0; q < RG; ++q) s[q][st] = MF::mma(kf, qf[q][ks], s[q][st]);
+        for (int q = 0; q < RG; ++q)
+          s[q][st] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf, qf[q][ks], s[q][st], 0, 0, 0);
       }
     }
     // Online softmax per query row (a lane owns one row of each group) with
@@ -277,46 +278,17 @@ __global__ __launch_bounds__(256) void attn_kernel(AttnArgs a) {
     }
 
     // O^T += V^T P^T; V^T fragments are shared by both row groups
-    if constexpr (kBF16) {
 #pragma unroll
-      for (int kc = 0; kc < NST / 2; ++kc) {
-        bf16x8 pf[RG];
+    for (int st = 0; st < NST; ++st)
 #pragma unroll
-        for (int q = 0; q < RG; ++q) {
-          u16x8 pb;
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            pb[r] = f32_to_bf16(s[q][2 * kc][r]);
-            pb[4 + r] = f32_to_bf16(s[q][2 * kc + 1][r]);
-          }
-          pf[q] = __builtin_bit_cast(bf16x8, pb);
-        }
+      for (int r = 0; r < 4; ++r)
 #pragma unroll
         for (int dt = 0; dt < NDT; ++dt) {
-          const T* vr = &sV[(16 * dt + l16) * LDV + 32 * kc + 4 * lg];
-          const u16x4 lo = *reinterpret_cast<const u16x4*>(vr);
-          const u16x4 hi = *reinterpret_cast<const u16x4*>(vr + 16);
-          const bf16x8 vf = __builtin_bit_cast(
-              bf16x8, u16x8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]});
+          const float vf = sV[(16 * dt + l16) * LDV + 16 * st + 4 * lg + r];
 #pragma unroll
           for (int q = 0; q < RG; ++q)
-            acc[q][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, pf[q], acc[q][dt], 0, 0, 0);
+            acc[q][dt] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf, s[q][st][r], acc[q][dt], 0, 0, 0);
         }
-      }
-    } else {
-#pragma unroll
-      for (int st = 0; st < NST; ++st)
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-#pragma unroll
-          for (int dt = 0; dt < NDT; ++dt) {
-            const float vf = (float)sV[(16 * dt + l16) * LDV + 16 * st + 4 * lg + r];
-#pragma unroll
-            for (int q = 0; q < RG; ++q)
-              acc[q][dt] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf, (float)s[q][st][r], acc[q][dt],
-                                                                0, 0, 0);
-          }
-    }
   }
 
   const size_t R = (size_t)a.B * a.tokens * a.n_q_heads;
@@ -1206,8 +1178,6 @@ __global__ __launch_bounds__(256) void attn_combine(const T* __restrict__ part_o
 
 template <typename T, int DH>
 void launch_dh(const AttnArgs& a, hipStream_t s, int parts) {
-  // 32-key tiles keep wide heads (and fp32) within the register file
-  constexpr int KT = (sizeof(T) == 2 && DH < 192) ? 64 : 32;
   const int G = a.n_q_heads / a.n_kv_heads;
   if (few_rows(a.B * a.tokens)) {
     if (parts & 1)
@@ -1223,7 +1193,7 @@ void launch_dh(const AttnArgs& a, hipStream_t s, int parts) {
     else if constexpr (sizeof(T) == 2)
       hipLaunchKernelGGL((attn16_kernel<DH, kAttn16Waves>), grid, dim3(64 * kAttn16Waves), 0, s, a);
     else
-      hipLaunchKernelGGL((attn_kernel<T, DH, KT, kRG>), grid, dim3(256), 0, s, a);
+      hipLaunchKernelGGL((attn_kernel<DH, 32, kRG>), grid, dim3(256), 0, s, a);
   }
   if (a.n_split > 1 && (parts & 2)) {
     const int R = a.B * a.tokens * a.n_q_heads;

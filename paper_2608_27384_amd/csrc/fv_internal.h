@@ -1,9 +1,8 @@
 // Internal declarations of the gfx950 streaming action-decode library.
 //
-// Element types: "bf16" tensors hold raw bf16 bit patterns (uint16_t); every
-// kernel is written once as a template over the storage type T (bf16_t or
-// float) and uses the matching MFMA instruction (16x16x32 bf16 or 16x16x4
-// fp32), so both precisions share one code path.
+// Element types: "bf16" tensors hold raw bf16 bit patterns (uint16_t); kernels
+// that serve both precisions are templates over the storage type T (bf16_t or
+// float) with the matching MFMA instruction.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -41,28 +40,8 @@ template <> __device__ __forceinline__ bf16_t from_f32<bf16_t>(float x) { return
 
 // ------------------------------------------------------------ MFMA operands
 // One 16x16 output tile: lane l holds rows 4*(l/16)+r (r = 0..3) of column
-// l%16.  An A-operand (B-operand) fragment holds KG consecutive k of row
-// (column) l%16 starting at k = KG*(l/16); one instruction covers KM = 4*KG k.
-template <typename T> struct Mfma;
-template <> struct Mfma<bf16_t> {
-  static constexpr int KG = 8, KM = 32;
-  typedef bf16x8 frag;
-  __device__ static __forceinline__ frag load(const bf16_t* p) {
-    return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u16x8*>(p));
-  }
-  __device__ static __forceinline__ f32x4 mma(frag a, frag b, f32x4 c) {
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
-  }
-};
-template <> struct Mfma<float> {
-  static constexpr int KG = 1, KM = 4;
-  typedef float frag;
-  __device__ static __forceinline__ frag load(const float* p) { return *p; }
-  __device__ static __forceinline__ f32x4 mma(frag a, frag b, f32x4 c) {
-    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-  }
-};
-
+// l%16.  An operand fragment holds k = l/16 of row (column) l%16 in fp32 and
+// the 8 consecutive k from 8*(l/16) in bf16.
 // A 16x16 product over one 64-byte k block (see tile_off), both operands as
 // 16-byte pieces.
 __device__ __forceinline__ f32x4 mma64(u32x4 x, u32x4 y, f32x4 c, bf16_t) {
@@ -216,8 +195,9 @@ __device__ __forceinline__ float gelu_tanh_f(float x) {
 // ------------------------------------------------------------ GEMM launches
 // C[M][N] = A[M][K] * Bt[N][K]^T with fp32 accumulation, followed by a fused
 // epilogue.  A is row-major with leading dimension K (tiled in a few-row
-// pass); Bt is the weight stored output-major ([out][in]) in the tiled layout.  Requirements: N % 128 == 0, K % 64 == 0 (bf16) or
-// K % 32 == 0 (fp32), 16-byte aligned base pointers.
+// pass); Bt is the weight stored output-major ([out][in]) in the tiled layout.
+// Requirements: N % 128 == 0, K % 64 == 0 (bf16) or K % 32 == 0 (fp32),
+// 16-byte aligned base pointers.
 struct GemmPlan {
   int tile = -1, ks = 1, tiles = 0;  // tile shape id, split-K factor, output tiles
   bool dma = false;                  // runs on the direct-to-LDS kernel (bf16)
@@ -363,8 +343,8 @@ struct EulerDest {
   int* n_valid;
   int K;
 };
-// Whether the few-row head (and the fused Euler update) applies.
-bool head_fusable(int rows, int W, int A);
+// Whether the velocity head can take the Euler update (at any row count).
+bool head_fusable(int W, int A);
 // The velocity head with the Euler update, emission, shift and refill of
 // launch_euler_shift fused in (same rounding, same noise); v is not stored.
 void launch_final_euler(const float* h, const float* mod, int mod_ld, int scale_off, int chunk_len,

@@ -1033,7 +1033,7 @@ void launch_time_embed(const float* t, T* e, int rows, int width, hipStream_t s,
                      width, period, K);
 }
 
-bool head_fusable(int rows, int W, int A) {
+bool head_fusable(int W, int A) {
   return W <= 1024 && W % 128 == 0 && A <= 32 && A % 4 == 0;
 }
 
@@ -1099,7 +1099,7 @@ void launch_final(const float* h, const float* mod, int mod_ld, int scale_off, i
                   float eps, const float* w_out, const float* w_out_t, const float* b_out, float* v,
                   int rows, int W, int A, hipStream_t s, const int* period) {
   const size_t lds = (size_t)(kFinalRows * W + 256 * kFinalRows) * sizeof(float);
-  if (rows >= kManyRows && head_fusable(rows, W, A)) {
+  if (rows >= kManyRows && head_fusable(W, A)) {
     hipLaunchKernelGGL(final_mma_kernel<false>, dim3(std::min(256, (rows + 15) / 16)), dim3(512), 0,
                        s, h, mod, mod_ld, scale_off, chunk_len, eps, w_out_t, b_out, v, rows, W, A,
                        EulerDest{}, period);

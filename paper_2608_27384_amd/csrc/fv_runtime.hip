@@ -293,7 +293,7 @@ bool enqueue_forward(Handle* h, const float* buffer, const float* t, int B, floa
   const int W = h->W, rowsT = B * h->T;
   const int Nmod = h->Nmod;
   const size_t layer_elems = (size_t)h->Bmax * h->Hkv * h->S * h->dh;
-  const bool fuse = eu && n_layers_run == h->L && head_fusable(rowsT, W, h->A);
+  const bool fuse = eu && n_layers_run == h->L && head_fusable(W, h->A);
   const float* mod = mod_cached;
   const int* per = mod_cached ? per_cached : nullptr;
   if (!mod) {
