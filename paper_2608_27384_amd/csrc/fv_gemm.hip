@@ -348,7 +348,7 @@ constexpr bool epi_staged() { return EpiStaged<Epi>::value; }
 // The loads are buffer loads (lds_dma16), and a k-step's fragments are read in
 // the order the MFMAs take them, so that the first MFMA waits for two reads,
 // not for all: gate/up at 32000 rows 535 -> 515 us, the projections with the
-// gated residual 262 -> 255, 10 packed buffers of 500 tokens 767 -> 727 us.
+// gated residual 262 -> 255.
 //   * 256x256, 8 waves (128x64 wave tiles), 2 stages: large M (batch 64);
 //   * 128x128, 8 waves and 64x128, 4 waves (32x64 wave tiles), 3 stages
 //     (2 for 128x128 grids of several rounds): medium M (batch 1), where the
@@ -643,11 +643,10 @@ struct EpiQkv {
   // (rows from row_hi on are the second stream's; pos_lo and pos_hi: rotary
   // position minus row of each).  Table and output addresses are a uniform
   // base and a 32-bit lane offset that moves by uniform steps from row to
-  // row: with an address of its own per element the epilogue took as many
-  // VALU cycles as the 1024-deep product takes MFMA cycles (3900 instructions
-  // a wave at 32000 rows; with it, 64 streams of 500 tokens, 2 layers, 3047 ->
-  // 3000 us, batch 1 of 18 layers 1375 -> 1367).  Rows past M read a clamped
-  // table entry and are not stored.
+  // row: an address of its own per element is a long VALU chain after the
+  // main loop (64 streams of 500 tokens, 2 layers, 3047 -> 3000 us together
+  // with the attention merge's slots by split count; a batch-1 step unchanged).
+  // Rows past M read a clamped table entry and are not stored.
   __device__ __forceinline__ void rotate_q(const f32x16& v0, const f32x16& v1, int row0, int c0,
                                            int lane, int M, int row_hi, int pos_lo,
                                            int pos_hi) const {
