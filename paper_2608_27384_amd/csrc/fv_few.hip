@@ -269,12 +269,17 @@ void few_launch(const T* A, const T* Bt, int M, int N, int K, int KS, const Epi&
 
 // Row tiles by M; 4 waves where a wave's share would fall under two k
 // blocks; two column groups per workgroup (they share the A fragments) once
-// one would give more than about 320 workgroups.
+// one would give more than about 320 workgroups; four in fp32 at 17 to 32 rows
+// past 1280 column groups (28672 columns, k 2048, 17 rows: 70 -> 57 us; 26624
+// columns, k 1024, 33.6 -> 33.3; slower in bf16 and at 16 rows or fewer).
 template <typename T, class Epi>
 void few_run(const T* A, const T* Bt, int M, int N, int K, int KS, const Epi& epi, hipStream_t s) {
   if (M <= 0) return;
   const int nb = K * (int)sizeof(T) / 64 / KS;
   const bool two = (long)(N / 16) * KS > 320 && N % 32 == 0;
+  if constexpr (sizeof(T) == 4)
+    if (M > 16 && M <= 32 && (long)(N / 16) * KS > 1280 && N % 64 == 0)
+      return few_launch<T, 2, 4, 8>(A, Bt, M, N, K, KS, epi, s);
 #define FV_FEW(RT)                                                   \
   if (nb <= 16 && !(two && RT > 2))                                   \
     two ? few_launch<T, RT, (RT > 2 ? 1 : 2), 4>(A, Bt, M, N, K, KS, epi, s) \

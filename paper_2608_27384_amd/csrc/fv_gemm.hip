@@ -1242,8 +1242,16 @@ void gemm_bias_f32(const T* A, const T* Bt, const float* bias, float* out, int M
       }
     }
   }
-  if (few_rows(M)) return few_bias_f32(A, Bt, bias, out, M, N, K, s, skip);
-  run_gemm(A, Bt, M, N, K, w, EpiBiasF32{out, bias, N, skip}, s);
+  // Every workgroup of the one-pass kernel reads all rows of A, so past 32 rows
+  // a wide product (the FiLM maps of more than a few layers) is faster on the
+  // tiles, one row tile and no split (bf16, width 1024, 64 rows: 18 layers, 112640
+  // columns, 86 us one-pass, 46 on tiles; 8192 columns 7.5 / 11.1; width 512,
+  // 13312 columns, 9.1 / 9.1 at 48 rows).
+  const bool wide = M > 32 && N > 16384;
+  if (few_rows(M) && !wide) return few_bias_f32(A, Bt, bias, out, M, N, K, s, skip);
+  const GemmPlan p = few_rows(M) ? tile_plan(M, N, K, sizeof(T) == 2, false)
+                                 : plan_gemm(M, N, K, sizeof(T) == 2);
+  run_tile(A, Bt, M, N, K, p, w, EpiBiasF32{out, bias, N, skip}, s);
 }
 template <typename T>
 void gemm_qkv(const T* A, const T* Bt, const QkvArgs<T>& qa, int M, int N, int K,

@@ -38,3 +38,25 @@ def test_wide_experts(shape):
             assert max(errs) < tol(w), (b, errs)
     finally:
         case.close()
+
+
+# (layers, chunks = FiLM rows of width 512, dtype): wide FiLM products on both
+# sides of 32 rows and 16384 columns, and of the fp32 kernel's four column groups
+FILM = [(4, 33, synth.BF16), (5, 33, synth.BF16), (6, 64, synth.BF16), (6, 32, synth.BF16),
+        (5, 48, synth.FP32), (7, 17, synth.FP32), (7, 32, synth.FP32), (7, 16, synth.FP32)]
+
+
+@pytest.mark.parametrize("shape", FILM, ids=lambda s: "x".join(map(str, s)))
+def test_wide_film_products(shape):
+    L, K, dtype = shape
+    w = synth.Workload("film", n_layers=L, width=512, n_q_heads=2, n_kv_heads=1, head_dim=64,
+                       mlp_dim=128, action_dim=8, chunk_len=2, n_chunks=K, prefix_len=9, batch=1,
+                       dtype=dtype)
+    case = Case(w)
+    try:
+        v, ref = case.gpu_velocity(), case.oracle_velocity(0)
+        errs = [rel_err(v[0, k], ref[k]) for k in range(K)]
+        print(shape, max(errs))
+        assert max(errs) < tol(w), errs
+    finally:
+        case.close()
