@@ -203,17 +203,16 @@ __global__ __launch_bounds__(64 * NW) void gemm_kernel(const T* __restrict__ A,
     for (int j = 0; j < FN; ++j) acc[i][j] = f32x16{};
 
   // Thread piece p: 16 bytes of row r, k-vector c of a stage (A rows first).
-  // Consecutive threads take consecutive vectors of a row, of the weights' tiles
-  // too, where a wave's load is still whole cache lines (8 rows by 8 vectors):
-  // their LDS stores are then one run (consecutive rows instead, 16 threads to
-  // a weight tile: fp32 products 2-3 % slower).
+  // Consecutive threads take consecutive vectors of a row of A, consecutive
+  // rows of a weight tile.
   const T* gp[NP];
   int lp[NP];
 #pragma unroll
   for (int p = 0; p < NP; ++p) {
     const bool isa = p < NA;
     const int vi = tid + NT * (isa ? p : p - NA);
-    const int r = vi >> 3, c = vi & 7;
+    const int r = isa ? vi >> 3 : (vi >> 7) * 16 + (vi & 15);
+    const int c = isa ? vi & 7 : (vi >> 4) & 7;
     gp[p] = isa ? A + (size_t)min(m0 + r, M - 1) * K + c * EPV
                 : Bt + tile_off<T>(n0 + r, c * EPV, K);
     lp[p] = (isa ? r : BM + r) * LDR + c * EPV;
