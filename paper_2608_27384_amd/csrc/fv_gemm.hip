@@ -204,7 +204,10 @@ __global__ __launch_bounds__(64 * NW) void gemm_kernel(const T* __restrict__ A,
 
   // Thread piece p: 16 bytes of row r, k-vector c of a stage (A rows first).
   // Consecutive threads take consecutive vectors of a row of A, consecutive
-  // rows of a weight tile.
+  // rows of a weight tile: its loads are then contiguous, which counts where the
+  // weights come from memory (fp32, 4 streams of 100 tokens, 4 layers of width
+  // 512: 426 us a pass, 433 with consecutive vectors of a row, though a product
+  // alone, its weights in cache, is 2-3 % slower).
   const T* gp[NP];
   int lp[NP];
 #pragma unroll
