@@ -634,7 +634,7 @@ __global__ __launch_bounds__(64 * NWV) void attn16_kernel(AttnArgs a) {
 //    and piece c of V^T row r at c ^ ((r / 4) % 4); the 16 rows one
 //    fragment read touches then fall on 16 different bank groups.
 // Bound by latency: two waves per SIMD (64 accumulator and 32 query registers
-// per 16 rows), MFMAs busy 31 % and LDS 49 % of the time at 64 streams.  The
+// per 16 rows), MFMAs busy 32 % of the time at 64 streams.  The
 // softmax without a per-tile maximum and lane exchange, the fixed order of
 // reads and MFMAs, and the buffer loads to LDS (waits for single fragments)
 // took 64 streams of 500 tokens from 356 to 334 us a layer; two workgroups of
